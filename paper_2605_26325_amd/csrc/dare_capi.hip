@@ -199,7 +199,7 @@ namespace {
 struct Group {
     std::vector<BatchReq> reqs;
     std::vector<int2> units;      // radii above 1: built here; radius 1: built on the device
-    int64_t nunits = 0;           // units (radius 1: the most the device may append)
+    int64_t nunits = 0;           // unit entries of the workspace (radius 1: the most the device may append)
 };
 
 // Batch workspace of one launch group: [header] [requests] [units] [tile records] [request
@@ -586,8 +586,8 @@ dare_status dare_reslice(const dare_volume* v, const dare_slice_spec* spec, floa
     DeviceGuard dg(v->device);
     const SliceArgs a = make_args(spec, out_dev);
     const int R = (int)v->p.radius_vox;
-    if (staged_radius(R)) return hip_status(launch_reslice_staged(v->dev, v->dtype, R, a, (hipStream_t)stream));
-    return hip_status(launch_reslice(v->dev, v->dtype, R, a, (hipStream_t)stream));
+    if (R > 1) return hip_status(launch_reslice_staged(v->dev, v->dtype, R, a, (hipStream_t)stream));
+    return hip_status(launch_reslice_tile(v->dev, v->dtype, a, (hipStream_t)stream));
 }
 
 uint64_t dare_reslice_batch_workspace_bytes(const dare_volume* const* vols, const dare_slice_spec* specs, int32_t n) {
@@ -639,9 +639,9 @@ dare_status run_batch(const dare_volume* const* vols, const dare_slice_spec* spe
         if (R <= 1) {
             g.nunits += tile_units_max(specs[k].width, specs[k].height);
         } else {
-            const int64_t u = batch_units(R, specs[k].width, specs[k].height);
+            const int64_t u = staged_tiles(specs[k].width, specs[k].height);
             for (int64_t t = 0; t < u; ++t) g.units.push_back(make_int2(r, (int)t));
-            g.nunits += u;
+            g.nunits += batch_units(R, specs[k].width, specs[k].height);
         }
         g.reqs.push_back(q);
     }
@@ -654,16 +654,17 @@ dare_status run_batch(const dare_volume* const* vols, const dare_slice_spec* spe
         const bool host_units = R > 1;
         const int nreq = (int)g.reqs.size();
         const GroupLayout L = group_layout(g.reqs.size(), (size_t)g.nunits, host_units);
-        host.assign(L.upload, 0);
+        const uint64_t bytes = host_units ? L.o_units + g.units.size() * sizeof(int2) : L.upload;
+        host.assign(bytes, 0);
         BatchHeader hd{};
-        hd.counts[0] = host_units ? (int)g.nunits : 0;
+        hd.counts[0] = host_units ? (int)g.units.size() : 0;
         hd.counts[1] = nreq;
         memcpy(host.data(), &hd, sizeof(hd));
         memcpy(host.data() + L.o_req, g.reqs.data(), g.reqs.size() * sizeof(BatchReq));
         if (host_units && !g.units.empty())
             memcpy(host.data() + L.o_units, g.units.data(), g.units.size() * sizeof(int2));
-        if (!upload(ws, host.data(), L.upload)) return DARE_ERR_HIP;
-        const int grid = R <= 1 ? kBatchGrid : (int)std::min<int64_t>(g.nunits, 65535);
+        if (!upload(ws, host.data(), bytes)) return DARE_ERR_HIP;
+        const int grid = R <= 1 ? kBatchGrid : (int)std::min<int64_t>((int64_t)g.units.size(), 65535);
         HIP_TRY(launch_reslice_batch(std::get<0>(kv.first), R, (const BatchReq*)(ws + L.o_req),
                                      (SliceRec*)(ws + L.o_rec), (int2*)(ws + L.o_units), (TileRec*)(ws + L.o_tiles),
                                      (int*)ws, nreq, (int)g.nunits, grid, stream));

@@ -1,6 +1,6 @@
 // Device helpers shared by the single-request reslice kernels and the batched passes:
 // slice setup (FP64 pose composition, Eq. 1 gates and Eq. 2 weights), FP64 pixel
-// positions, the per-pixel gather of a trilinear cell, and the radius >= 2 unit.
+// positions and the per-pixel gather of a trilinear cell.
 #pragma once
 
 #include <math.h>
@@ -29,6 +29,26 @@ __device__ __forceinline__ double uniform_f64(double x) {
 }
 
 __device__ __forceinline__ int uniform_i32(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Pointers in the global address space, so that loads and stores through them are global (not
+// flat) operations, whose waits do not wait for LDS and vice versa.
+template <class T>
+using gptr = __attribute__((address_space(1))) T*;
+template <class T>
+__device__ __forceinline__ gptr<T> global(T* p) {
+    return (gptr<T>)(p);
+}
+
+// Workgroup-uniform values, moved to scalar registers.
+__device__ __forceinline__ int ui(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uf(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+__device__ __forceinline__ double ud(double x) { return uniform_f64(x); }
+
+// Entry i of a 3-vector held in registers, without indexing it (which would put it in memory).
+template <class T>
+__device__ __forceinline__ T pick3(const T (&v)[3], int i) {
+    return i == 0 ? v[0] : (i == 1 ? v[1] : v[2]);
+}
 
 // The slice pose T = P.C, rows 0..2 (every lane the same).
 __device__ __forceinline__ void slice_pose(const VolDev* __restrict__ vd, const SliceArgs& s, double T[12]) {
@@ -191,8 +211,6 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
     return (bid & 7) * (nblocks >> 3) + (bid >> 3);
 }
 
-constexpr int kBinChunk = 16;        // gathers issued together per voxel
-
 // Division by a divisor shared by a workgroup, for small dividends: x / d = the high word of
 // x * m with m = ceil(2^32 / d), exact for 0 <= x < 2^16 and 2 <= d < 2^16 (m exceeds 2^32 / d
 // by less than 1, which moves x * m / 2^32 by less than 2^-16, less than the 1/d gap between
@@ -215,6 +233,44 @@ __device__ __forceinline__ int sdiv(int x, SmallDiv s) {
     return s.d == 1 ? x : (int)__umulhi((uint32_t)x, s.m);
 }
 
+__device__ __forceinline__ SmallDiv usd(uint32_t m, int d) { return SmallDiv{(uint32_t)ui((int)m), ui(d)}; }
+
+// The bits that voxel coordinate v along axis A contributes to its brick-local index: the index
+// interleaves the coordinates' bits, so it is the sum (an OR of disjoint fields) of one part per
+// axis, and a list entry can add the dominant axis's part to a per-column remainder.
+template <int A>
+__host__ __device__ constexpr int local_part(int v) {
+    return A == 0 ? ((v & 6) << 6) | (v & 1) : (A == 1 ? ((v & 6) << 4) | ((v & 1) << 1) : (v & 7) << 2);
+}
+constexpr bool local_parts_match() {
+    for (int x = 0; x < 8; ++x)
+        for (int y = 0; y < 8; ++y)
+            for (int z = 0; z < 8; ++z)
+                if (brick_local(x, y, z) != (local_part<0>(x) | local_part<1>(y) | local_part<2>(z))) return false;
+    return true;
+}
+static_assert(local_parts_match(), "the brick-local index is the sum of its per-axis parts");
+
+// First voxel of the run of column (vp, vq): the first whole voxel above centre - half, where
+// centre is the plane's coordinate along DAX at the column (FP32 about the tile's origin c0).
+// The column's voxels with |m.(v - c0)| < thr_n are among the depth voxels from there.
+template <int DAX>
+__device__ __forceinline__ int run_start(const float (&c0)[3], const float (&m)[3], float inv_md, float half, int vp,
+                                         int vq) {
+    constexpr int PAX = DAX == 0 ? 1 : 0, QAX = DAX == 2 ? 1 : 2;
+    const float centre = c0[DAX] - (m[PAX] * ((float)vp - c0[PAX]) + m[QAX] * ((float)vq - c0[QAX])) * inv_md;
+    return (int)floorf(centre - half) + 1;
+}
+
+// Bins past the survivors: no slots, zero weight (one wave, lane b for bin b).
+__device__ __forceinline__ void pad_bins(SetupLds& rec, int kact) {
+    const int lane = threadIdx.x & 63;
+    if (lane >= kact) {
+        rec.act_bin[lane] = 0;
+        rec.act_w[lane] = 0.0f;
+    }
+}
+
 __device__ __forceinline__ VolView view_of(const VolDev* __restrict__ vd) {
     VolView v;
     v.table = vd->table;
@@ -233,16 +289,6 @@ __device__ __forceinline__ VolView view_of(const VolDev* __restrict__ vd) {
     return v;
 }
 
-// Tent weight 1 - |o - f| / R of the voxel at integer offset o (-R < o <= R) from the cell floor
-// along one axis, for a sample at fraction f of its cell, with g = 1 - f.  Both come from the
-// FP64 position (f = c - floor(c), g = floor(c) + 1 - c), and the low side (o <= 0) is written
-// through g: as f nears 1 it rounds to 1 in FP32 while g stays positive, so a voxel whose FP64
-// weight is positive keeps a positive weight (and a pixel whose only valid voxels lie there stays
-// assigned, as in FP64).
-__device__ __forceinline__ float tent_weight(int o, float f, float g, int R, float invR) {
-    return o <= 0 ? fmaxf(0.0f, ((float)(R - 1 + o) + g) * invR) : fmaxf(0.0f, ((float)(R - o) + f) * invR);
-}
-
 // Per-pixel gather of the 8 cell voxels over the surviving bins (no staging).  The whole
 // workgroup works on one request: bin ids and weights are broadcast as scalars.  All loads of
 // NB bins are issued before any is used (indices of absent voxels point at entry 0, which
@@ -254,7 +300,9 @@ __device__ __forceinline__ float pixel_direct(const VolView& vv, const SetupLds&
     const double f0 = floor(c[0]), f1 = floor(c[1]), f2 = floor(c[2]);
     const int x0 = (int)f0, y0 = (int)f1, z0 = (int)f2;
     const float fx = (float)(c[0] - f0), fy = (float)(c[1] - f1), fz = (float)(c[2] - f2);
-    // the low voxel's weight from FP64 (tent_weight at R = 1)
+    // the low voxel's weight 1 - f from the FP64 position: as f nears 1 it rounds to 1 in FP32
+    // while 1 - f stays positive, so a voxel whose FP64 weight is positive keeps a positive weight
+    // (and a pixel whose only valid voxels lie there stays assigned, as in FP64)
     const float gx = (float)(f0 + 1.0 - c[0]), gy = (float)(f1 + 1.0 - c[1]), gz = (float)(f2 + 1.0 - c[2]);
     const float wx[2] = {gx, fx}, wy[2] = {gy, fy}, wz[2] = {gz, fz};
     const int nbx = vv.nbx, nby = vv.nby;
@@ -327,86 +375,6 @@ __device__ __forceinline__ float pixel_direct(const VolView& vv, const SetupLds&
                 }
             }
     return den > 0.0f ? num / den : __builtin_nanf("");
-}
-
-// ---------------------------------------------------------------- radius R >= 2: lane-split neighbourhood
-template <int DT, int G>
-__device__ __forceinline__ void reslice_unit_rn(const VolDev* __restrict__ vd, const SliceArgs& s, int unit,
-                                                SetupLds& sh) {
-    using PT = Pair<DT>;
-    constexpr int PPW = 256 / G;   // pixels per workgroup
-    if (threadIdx.x < 64) {
-        double T[12];
-        slice_setup(vd, s, sh, T);
-    }
-    __syncthreads();
-    SlicePos q;
-    load_pos(vd, sh, s, q);
-    const int kact = uniform_i32(sh.kact);
-    const int R = vd->radius;
-    const float invR = 1.0f / (float)R;
-    const int g = threadIdx.x % G;
-    const int64_t pix = (int64_t)unit * PPW + threadIdx.x / G;
-    const bool live = pix < (int64_t)s.W * s.H;
-    const int i = live ? (int)(pix % s.W) : 0;
-    const int j = live ? (int)(pix / s.W) : 0;
-    const int nx = vd->nx, ny = vd->ny, nz = vd->nz;
-    double c[3];
-    pixel_coords(q, i, j, c);
-    const bool near = live && kact > 0 && c[0] > -(double)R && c[0] < (double)(nx - 1 + R) && c[1] > -(double)R &&
-                      c[1] < (double)(ny - 1 + R) && c[2] > -(double)R && c[2] < (double)(nz - 1 + R);
-    float num = 0.0f, den = 0.0f;
-    if (near) {
-        const double f0 = floor(c[0]), f1 = floor(c[1]), f2 = floor(c[2]);
-        const int x0 = (int)f0, y0 = (int)f1, z0 = (int)f2;
-        const float fr[3] = {(float)(c[0] - f0), (float)(c[1] - f1), (float)(c[2] - f2)};
-        const float gr[3] = {(float)(f0 + 1.0 - c[0]), (float)(f1 + 1.0 - c[1]), (float)(f2 + 1.0 - c[2])};
-        const int span = 2 * R;
-        const int nbx = vd->nbx, nby = vd->nby;
-        const typename PT::T* __restrict__ data = (const typename PT::T*)vd->data;
-        const int64_t nbricks = vd->nbricks;
-        for (int r = g; r < span * span; r += G) {
-            const int oz = r / span - R + 1, oy = r % span - R + 1;
-            const int vz = z0 + oz, vy = y0 + oy;
-            if ((unsigned)vz >= (unsigned)nz || (unsigned)vy >= (unsigned)ny) continue;
-            const float tz = tent_weight(oz, fr[2], gr[2], R, invR);
-            const float ty = tent_weight(oy, fr[1], gr[1], R, invR);
-            const float tyz = ty * tz;
-            if (!(tyz > 0.0f)) continue;
-            const int rb = ((vz >> 3) * nby + (vy >> 3)) * nbx;
-            for (int ox = -R + 1; ox <= R; ++ox) {
-                const int vx = x0 + ox;
-                if ((unsigned)vx >= (unsigned)nx) continue;
-                const float tx = tent_weight(ox, fr[0], gr[0], R, invR);
-                const float t = tx * tyz;
-                if (!(t > 0.0f)) continue;
-                float A = 0.0f, B = 0.0f;
-                for (int k = 0; k < kact; ++k) {
-                    const int b = uniform_i32(sh.act_bin[k]);
-                    const int slot = vd->table[(int64_t)b * nbricks + rb + (vx >> 3)];
-                    if (slot < 0) continue;
-                    float2 sc = make_float2(0.0f, 0.0f);
-                    if constexpr (DT == DARE_FP8_E4M3) sc = vd->scales[slot];
-                    float a, cnt;
-                    PT::decode(data[(size_t)slot * kBrickVox + brick_local(vx, vy, vz)], sc, a, cnt);
-                    const float wc = sh.act_w[k] * cnt;
-                    A = __builtin_fmaf(wc, a, A);
-                    B = B + wc;
-                }
-                if (B > 0.0f) {
-                    num = __builtin_fmaf(t, A / B, num);
-                    den = den + t;
-                }
-            }
-        }
-    }
-    // combine the G lanes of this pixel
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) {
-        num += __shfl_xor(num, off, G);
-        den += __shfl_xor(den, off, G);
-    }
-    if (live && g == 0) s.out[(size_t)j * s.W + i] = den > 0.0f ? num / den : __builtin_nanf("");
 }
 
 }  // namespace

@@ -1,13 +1,31 @@
-// Directionality-aware reslice at interpolation radius R = 2..4 voxels (Sec. 2.1 "Reslicing",
+// Directionality-aware reslice at interpolation radius R = 2..8 voxels (Sec. 2.1 "Reslicing",
 // Eq. 1, Eq. 2, Fig. 2; the paper times radii of 0.125, 0.25 and 0.5 mm).
 //
 // Every pixel blends the voxels within L-infinity distance R of its position with tent weights
 // prod_a max(0, 1 - |c_a - v_a| / R), (2R)^3 voxels per pixel, each voxel's value being its
-// direction blend V_v = sum_b w_b c_vb a_vb / sum_b w_b c_vb over the surviving bins.  V_v does
-// not depend on the pixel, and at these radii neighbouring pixels share almost all of their
-// voxels, so one workgroup per 16x16 tile blends every voxel the tile reaches once into LDS
-// (the radius-1 scheme with the reach widened by R), then each pixel sums its (2R)^3 values
-// from LDS.  Tiles whose voxel box exceeds the LDS budget (coarse output pitch) gather per pixel.
+// direction blend V_v = sum_b w_b c_vb a_vb / sum_b w_b c_vb over the surviving bins.
+//
+// The tents are not summed per pixel.  A tent of integer half-width R has its corners on whole
+// voxels, so along each axis it is linear between two neighbouring lattice points, and the sums
+// over voxels, N(c) = sum_v t_v(c) V_v and D(c) = sum_v t_v(c) over the valid voxels, are
+// trilinear in every unit cell: they are the trilinear interpolation of their own values at the
+// cell's 8 corners.  At a lattice point g the weights are products of the whole numbers
+// R - |g_a - v_a| (the common factor R^-3 cancels in N / D), so N and D on the lattice are
+// separable convolutions of 2R - 1 taps per axis.  A tile computes
+//   voxels   V_v of every voxel its pixels reach, once, into LDS (NaN where not valid);
+//   lattice  N and D at the cells' corners by three passes of 2R - 1 taps in LDS, along the
+//            dominant axis of the normal first (the axis whose extent shrinks most);
+//   pixels   N and D interpolated from 8 corners, and their quotient.
+// D at a lattice point is a whole number (at most R^6 < 2^24) and exact in FP32, and a pixel is
+// assigned exactly when a voxel with positive weight is valid, as in the direct sum: a corner's
+// weight is positive where the voxel range of its tents adds to the pixel's.  A lattice value
+// with positive weight for a pixel does not depend on the tile (every voxel within its tents is in
+// the pixel's reach and so staged, and taps are added in a fixed order), so a request gives the
+// same bits alone and in a batch, whatever the tile edge.
+//
+// One workgroup takes a 16 x 16 tile, in one piece if its voxel box fits the LDS budget and in
+// pieces of 8, 4, 2 or 1 pixels squared if not (coarse output pitch).  A single pixel's box
+// always fits.
 #include "dare_reslice_dev.h"
 #include "dare_staged.h"
 
@@ -16,393 +34,561 @@ namespace dare {
 namespace {
 
 template <int R>
-struct RsLimits {
-    static constexpr int kEdge = 13 + 2 * R;                    // box voxels per axis at 0.5-voxel pitch
-    static constexpr int kBoxMax = kEdge * kEdge * kEdge;       // LDS values per tile
-    static constexpr int kSlotMax = 2048;                       // (surviving bin, box brick) slots
+struct WideLimits {
+    // The pool holds V and, in the place it leaves, the second pass's output; and beside them the
+    // cube list and, in its place, the outputs of the first and third pass.  A 16 x 16 tile at half
+    // a voxel per pixel has at most 11 lattice points per axis, however it lies.  Up to radius 6
+    // the pool is a little less than that takes, so that more workgroups fit a CU: 6, 5, 4, 2, 2 at
+    // R = 2..6 (a 512 x 512 slice has 4 tiles per CU; at R = 4 the full pool allowed 3 workgroups,
+    // a second round, and 39 us per slice against 27); the steepest tiles then go in pieces.
+    static constexpr int kLattice = 11, kEdge = kLattice + 2 * R - 2;
+    static constexpr int kFull = (kEdge * kEdge * kEdge + 2 * kLattice * kEdge * kEdge + 11) / 4 * 4;   // V, first pass
+    static constexpr int kPool = R == 2 ? 5400 : R == 3 ? 6600 : R == 4 ? 8900 : R == 5 ? 14800 : R == 6 ? 17600 : kFull;
+    static constexpr int kSlots = R <= 4 ? 1024 : 2048;     // (box brick, bin) table entries: one pixel's, at 64 bins
+    static constexpr int kThreads = R <= 4 ? 256 : 512;     // boxes of 10000 voxels: two workgroups per CU
+    static_assert(kPool % 4 == 0 && kPool >= 8 * R * R * R + 16 * R * R + 8, "a single pixel's box fits");
+    static_assert(((2 * R + 6) / 8 + 1) * ((2 * R + 6) / 8 + 1) * ((2 * R + 6) / 8 + 1) * kMaxBins <= kSlots, "and its slots");
 };
 
+// A list entry packs a 2 x 2 x 2 cube's place in its brick (6 bits), its box brick (9) and its
+// coordinates among the box's cubes (5 each).
+constexpr int kBoxBricks = 511, kBoxEdge = 60;
+
 template <int DT, int R>
-struct TileLdsR {
-    int mode;                        // 0: nothing in reach, 1: staged, 2: per-pixel gather
-    int lo[3], dim[3];
-    int blo[3], bdim[3], nbb;
-    int dax, pax, qax;
-    int depth, ncols;
-    float m[3], c0[3], ua[3], va[3];
-    float thr_n, thr_u, thr_v, len_u, len_v, inv_md;
+struct WideLds {
+    SetupLds sh;
     int nlist;
-    int slot[RsLimits<R>::kSlotMax];
-    float2 scale[DT == DARE_FP8_E4M3 ? RsLimits<R>::kSlotMax : 1];
-    float V[RsLimits<R>::kBoxMax];
-    unsigned short list[RsLimits<R>::kBoxMax];
+    alignas(16) int slot[WideLimits<R>::kSlots];             // [box brick][bin], rows of kactp
+    float2 scale[DT == DARE_FP8_E4M3 ? WideLimits<R>::kSlots : 1];
+    alignas(16) float pool[WideLimits<R>::kPool];
 };
 
-// Wave 0: the tile's voxel box (its corner pixels' cells widened by R, one voxel of margin)
-// and the footprint tests scaled by R.
-template <int DT, int R>
-__device__ __forceinline__ void tile_setup_r(const VolDev* __restrict__ vd, const SliceArgs& s, const double T[12],
-                                             const SetupLds& sh, int kact, int i0, int j0, TileLdsR<DT, R>& tl) {
-    const int lane = threadIdx.x;
-    const int i1 = min(i0 + kTile - 1, s.W - 1), j1 = min(j0 + kTile - 1, s.H - 1);
-    SlicePos q;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        q.t[a] = T[a * 4 + 3];
-        q.e0[a] = T[a * 4 + 0];
-        q.e1[a] = T[a * 4 + 1];
-        q.o[a] = vd->origin[a];
-    }
-    q.inv_h = vd->inv_h;
-    q.sx = s.sx;
-    q.sy = s.sy;
-    const int n[3] = {vd->nx, vd->ny, vd->nz};
-    const int k = lane & 3;
+// Minimum over the four lanes of a quad.
+__device__ __forceinline__ int quad_min(int x) {
+    x = min(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true));
+    return min(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true));
+}
+
+// The lattice points of a tile's cells: `lat` the lowest cell floor, `len` lattice points per
+// axis; c0 the first pixel's position.  Positions are rounded sums and products, so they rise (or
+// fall) with i and with j each, and the corner pixels' cells bound every pixel's exactly.  The
+// lanes of each quad take the four corners.
+__device__ __forceinline__ void tile_cells(const SlicePos& q, int i0, int j0, int i1, int j1, int (&lat)[3],
+                                           int (&len)[3], float (&c0)[3]) {
+    const int k = threadIdx.x & 3;
     double c[3];
     pixel_coords(q, (k & 1) ? i1 : i0, (k & 2) ? j1 : j0, c);
-    int lo[3], hi[3];
-    float c0[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int f = (int)fmin(fmax(floor(c[a]), -1048576.0), 1048576.0);
-        int mn = f, mx = f;
-#pragma unroll
-        for (int o = 1; o < 4; ++o) {
-            const int g = __shfl(f, o, 4);
-            mn = min(mn, g);
-            mx = max(mx, g);
-        }
-        lo[a] = max(mn - R, 0);
-        hi[a] = min(mx + R + 1, n[a] - 1);
-        c0[a] = (float)__shfl(c[a], 0, 4);
+        lat[a] = ui(quad_min(f));
+        len[a] = -ui(quad_min(-f)) - lat[a] + 2;
+        c0[a] = uf((float)c[a]);   // lane 0 of the wave: the first pixel
     }
-    if (lane != 0) return;
-    int mode = kact > 0 ? 1 : 0;
-    int nvox = 1, nbb = 1;
-    float l1m = 0.0f, l1u = 0.0f, l1w = 0.0f;
+}
+
+// Does a tile with these lattice extents fit the LDS budget?
+template <int R>
+__device__ __forceinline__ bool wide_fits(const int (&len)[3], int dax, int kactp) {
+    using L = WideLimits<R>;
+    const int pax = dax == 0 ? 1 : 0, qax = dax == 2 ? 1 : 2;
+    int l[3], v[3], nbb = 1, ncubes = 1;
+    bool small = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (lo[a] > hi[a]) mode = 0;
-        const int d = hi[a] - lo[a] + 1;
-        tl.lo[a] = lo[a];
-        tl.dim[a] = d > 0 ? d : 0;
-        nvox *= tl.dim[a];
-        tl.blo[a] = lo[a] >> 3;
-        tl.bdim[a] = d > 0 ? (hi[a] >> 3) - (lo[a] >> 3) + 1 : 0;
-        nbb *= tl.bdim[a];
-        tl.m[a] = sh.fm[a];
-        tl.ua[a] = sh.fu[a];
-        tl.va[a] = sh.fw[a];
-        tl.c0[a] = c0[a];
-        l1m += fabsf(sh.fm[a]);
-        l1u += fabsf(sh.fu[a]);
-        l1w += fabsf(sh.fw[a]);
+        l[a] = min(len[a], 64);
+        v[a] = l[a] + 2 * R - 2;
+        nbb *= (v[a] + 6) / 8 + 1;
+        ncubes *= v[a] / 2 + 1;
+        small = small && v[a] <= kBoxEdge;
     }
-    if (mode == 1 && (nvox > RsLimits<R>::kBoxMax || kact * nbb > RsLimits<R>::kSlotMax)) mode = 2;
-    tl.mode = mode;
-    tl.nbb = nbb;
+    const int ld = pick3(l, dax), lp = pick3(l, pax), vp = pick3(v, pax), vq = pick3(v, qax);
+    const int nv = v[0] * v[1] * v[2], p1 = 2 * ld * vp * vq, p2 = 2 * ld * lp * vq;
+    return small && max(nv, p2) + max(ncubes, p1) + 8 <= L::kPool && nbb <= kBoxBricks && nbb * kactp <= L::kSlots;
+}
+
+// One tile piece of pixels, workgroup-uniform.
+struct Piece {
+    int i0, j0, ni, nj;
+    int lat[3], len[3];     // lattice points
+    int lo[3], dim[3];      // voxel box (may leave the grid)
+    int blo[3], bdim[3];    // its in-grid bricks
+    float c0[3];
+};
+
+// Voxels phase, first part: the cubes of 2 x 2 x 2 voxels (one 64-byte line of FP32 pairs, 32 bytes
+// of BF16) that may hold a voxel in reach, one thread per cube, z fastest as in the bricks; those
+// that pass are listed in that order, with one LDS atomic per wave.
+template <int DT, int R, int NT>
+__device__ __forceinline__ void list_cubes(const VolView& vv, const Piece& t, WideLds<DT, R>& L, int* list) {
+    float m[3], fu[3], fw[3], l1m = 0.0f, l1u = 0.0f, l1w = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        m[a] = uf(L.sh.fm[a]);
+        fu[a] = uf(L.sh.fu[a]);
+        fw[a] = uf(L.sh.fw[a]);
+        l1m += fabsf(m[a]);
+        l1u += fabsf(fu[a]);
+        l1w += fabsf(fw[a]);
+    }
     // a voxel within L-infinity distance R of a pixel p of the tile satisfies |m.(v - p)| < R |m|_1,
-    // and its lateral offsets exceed the tile's extent by less than R |ua|_1, R |va|_1
-    const int dax = sh.dax;
-    tl.thr_n = (float)R * l1m + 2e-3f;
-    tl.thr_u = (float)R * l1u + 0.02f;
-    tl.thr_v = (float)R * l1w + 0.02f;
-    tl.len_u = (float)(i1 - i0) * sh.lu;
-    tl.len_v = (float)(j1 - j0) * sh.lw;
-    tl.dax = dax;
-    tl.pax = dax == 0 ? 1 : 0;
-    tl.qax = dax == 2 ? 1 : 2;
-    tl.inv_md = 1.0f / sh.fm[dax];
-    // a column's voxels in reach are the integers in (centre - half, centre + half), half =
-    // thr_n / |m[dax]|: at most ceil(2 half) of them, the first one above centre - half
-    tl.depth = mode == 1 ? (int)ceilf(2.0f * (tl.thr_n * fabsf(tl.inv_md))) : 0;
-    tl.ncols = mode == 1 ? tl.dim[tl.pax] * tl.dim[tl.qax] : 0;
-    tl.nlist = 0;
-}
-
-// V_v of one voxel from the staged brick slots; NaN when no surviving bin holds a sample.
-template <int DT, int R>
-__device__ __forceinline__ float blend_voxel_r(const typename Pair<DT>::T* __restrict__ data, const SetupLds& sh,
-                                               const TileLdsR<DT, R>& tl, int kact, int bb, int local) {
-    using PT = Pair<DT>;
-    const int nbb = tl.nbb;
-    if (kact == 1) {
-        const int slot = tl.slot[bb];
-        if (slot < 0) return __builtin_nanf("");
-        float2 sc = make_float2(0.0f, 0.0f);
-        if constexpr (DT == DARE_FP8_E4M3) sc = tl.scale[bb];
-        float a, cnt;
-        PT::decode(data[(size_t)slot * kBrickVox + local], sc, a, cnt);
-        return cnt > 0.0f ? a : __builtin_nanf("");
+    // and its lateral offsets exceed the tile's extent by less than R |u|_1, R |w|_1; a cube's voxels
+    // lie within 1/2 of its centre (the margins cover FP32 rounding of coordinates up to the grid's
+    // size and the pose rigidity tolerance)
+    const float slop = 2e-3f + 1e-6f * (float)(max(vv.n[0], max(vv.n[1], vv.n[2])) + 64);
+    const float reach = (float)R + 0.5f;
+    const float thr_n = reach * l1m + slop, thr_u = reach * l1u + 0.02f + slop, thr_v = reach * l1w + 0.02f + slop;
+    const float hi_u = (float)(t.ni - 1) * uf(L.sh.lu) + thr_u, hi_v = (float)(t.nj - 1) * uf(L.sh.lw) + thr_v;
+    int c_lo[3], c_n[3];      // the cubes of the box inside the grid
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        c_lo[a] = max(t.lo[a], 0) >> 1;
+        c_n[a] = ((min(t.lo[a] + t.dim[a], vv.n[a]) - 1) >> 1) - c_lo[a] + 1;
     }
-    float A = 0.0f, B = 0.0f;
-    for (int k0 = 0; k0 < kact; k0 += kBinChunk) {
-        int sl[kBinChunk];
-        typename PT::T p[kBinChunk];
+    const int n = c_n[0] * c_n[1] * c_n[2];
+    const SmallDiv dz = small_div(c_n[2]), dy = small_div(c_n[1]);
+    for (int base = 0; base < n; base += NT) {
+        const int e = base + (int)threadIdx.x;
+        const int exy = sdiv(e, dz), cx = sdiv(exy, dy);
+        const int c[3] = {c_lo[0] + cx, c_lo[1] + exy - cx * c_n[1], c_lo[2] + e - exy * c_n[2]};
+        float dn = 0.0f, du = 0.0f, dv = 0.0f;
 #pragma unroll
-        for (int u = 0; u < kBinChunk; ++u) sl[u] = (k0 + u < kact) ? tl.slot[(k0 + u) * nbb + bb] : -1;
-#pragma unroll
-        for (int u = 0; u < kBinChunk; ++u)
-            if (sl[u] >= 0) p[u] = data[(size_t)sl[u] * kBrickVox + local];
-#pragma unroll
-        for (int u = 0; u < kBinChunk; ++u) {
-            if (sl[u] < 0) continue;
-            float2 sc = make_float2(0.0f, 0.0f);
-            if constexpr (DT == DARE_FP8_E4M3) sc = tl.scale[(k0 + u) * nbb + bb];
-            float a, cnt;
-            PT::decode(p[u], sc, a, cnt);
-            const float wc = sh.act_w[k0 + u] * cnt;
-            A = __builtin_fmaf(wc, a, A);
-            B = B + wc;
+        for (int a = 0; a < 3; ++a) {
+            const float d = (float)(2 * c[a]) + 0.5f - t.c0[a];
+            dn += m[a] * d;
+            du += fu[a] * d;
+            dv += fw[a] * d;
+        }
+        const bool pass =
+            e < n && fabsf(dn) < thr_n && du > -thr_u && du < hi_u && dv > -thr_v && dv < hi_v;
+        const unsigned long long mask = __ballot(pass);
+        int first = 0;
+        if ((threadIdx.x & 63) == 0 && mask) first = atomicAdd(&L.nlist, __popcll(mask));
+        first = ui(first);
+        if (pass) {
+            const int box = (((c[2] >> 2) - t.blo[2]) * t.bdim[1] + (c[1] >> 2) - t.blo[1]) * t.bdim[0] + (c[0] >> 2) - t.blo[0];
+            list[first + __popcll(mask & ((1ull << (threadIdx.x & 63)) - 1ull))] =
+                (brick_local(2 * c[0], 2 * c[1], 2 * c[2]) >> 3) | box << 6 | (c[0] - (t.lo[0] >> 1)) << 15 |
+                (c[1] - (t.lo[1] >> 1)) << 20 | (c[2] - (t.lo[2] >> 1)) << 25;
         }
     }
-    return B > 0.0f ? A / B : __builtin_nanf("");
 }
 
-// The same V_v read straight from the volume (tiles that gather per pixel): the arithmetic and
-// its order are blend_voxel_r's.
-template <int DT>
-__device__ __forceinline__ float voxel_value(const VolDev* __restrict__ vd, const SetupLds& sh, int kact, int vx,
-                                             int vy, int vz) {
+// Voxels phase, second part: the listed cubes' voxels, eight lanes per cube (so a wave reads whole
+// lines of a bin), their surviving bins gathered and blended into V_v, NaN when none holds a
+// sample.  U voxels of NB bins per thread and round: their pair loads are all issued before any is
+// used; a pair with no slot is skipped and adds nothing.
+template <int DT, int R, int NT>
+__device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, int dax, WideLds<DT, R>& L,
+                                            const int* list, float* V, int kact, int kactp) {
     using PT = Pair<DT>;
-    const typename PT::T* __restrict__ data = (const typename PT::T*)vd->data;
-    const int64_t nbricks = vd->nbricks;
-    const int64_t brick = ((int64_t)(vz >> 3) * vd->nby + (vy >> 3)) * vd->nbx + (vx >> 3);
-    const int local = brick_local(vx, vy, vz);
-    if (kact == 1) {
-        const int slot = vd->table[(int64_t)sh.act_bin[0] * nbricks + brick];
-        if (slot < 0) return __builtin_nanf("");
-        float2 sc = make_float2(0.0f, 0.0f);
-        if constexpr (DT == DARE_FP8_E4M3) sc = vd->scales[slot];
-        float a, cnt;
-        PT::decode(data[(size_t)slot * kBrickVox + local], sc, a, cnt);
-        return cnt > 0.0f ? a : __builtin_nanf("");
+    using T = typename PT::T;
+    constexpr int U = 2, NB = 8;
+    const gptr<const T> data = global((const T*)vv.data);
+    const uint32_t cap = (uint32_t)ui((int)vv.cap);
+    const int nvox = 8 * ui(L.nlist);
+    // V's strides per axis, the lane's place in a cube, and the in-grid part of the box
+    const int pax = dax == 0 ? 1 : 0;
+    const int vd = pick3(t.dim, dax), vdp = vd * pick3(t.dim, pax);
+    int str[3], off[3], r0[3], rn[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        str[a] = a == dax ? 1 : (a == pax ? vd : vdp);
+        off[a] = (((int)threadIdx.x >> a) & 1) - (t.lo[a] & 1);
+        r0[a] = max(-t.lo[a], 0);
+        rn[a] = min(t.dim[a], vv.n[a] - t.lo[a]) - r0[a];
     }
-    float A = 0.0f, B = 0.0f;
-    for (int k = 0; k < kact; ++k) {
-        const int slot = vd->table[(int64_t)sh.act_bin[k] * nbricks + brick];
-        if (slot < 0) continue;
-        float2 sc = make_float2(0.0f, 0.0f);
-        if constexpr (DT == DARE_FP8_E4M3) sc = vd->scales[slot];
-        float a, cnt;
-        PT::decode(data[(size_t)slot * kBrickVox + local], sc, a, cnt);
-        const float wc = sh.act_w[k] * cnt;
-        A = __builtin_fmaf(wc, a, A);
-        B = B + wc;
-    }
-    return B > 0.0f ? A / B : __builtin_nanf("");
-}
-
-// One 16x16 tile at radius R.
-template <int DT, int R>
-__device__ __forceinline__ void reslice_tile_rs(const VolDev* __restrict__ vd, const SliceArgs& s, int unit,
-                                                SetupLds& sh, TileLdsR<DT, R>& tl) {
-    const int tx = unit % s.tiles_x, ty = unit / s.tiles_x;
-    const int i0 = tx * kTile, j0 = ty * kTile;
-    if (threadIdx.x < 64) {
-        double T[12];
-        const int ka = slice_setup(vd, s, sh, T);
-        tile_setup_r<DT, R>(vd, s, T, sh, ka, i0, j0, tl);
-    }
-    __syncthreads();
-    const int kact = uniform_i32(sh.kact);
-    const int mode = uniform_i32(tl.mode);
-    if (mode == 1) {
-        // (a) brick slots (and FP8 scales) of every surviving bin over the box's bricks
-        const int nbb = tl.nbb;
-        const int64_t nbricks = vd->nbricks;
-        for (int e = threadIdx.x; e < kact * nbb; e += blockDim.x) {
-            const int k = e / nbb, r = e - k * nbb;
-            const int bxx = r % tl.bdim[0], byz = r / tl.bdim[0];
-            const int byy = byz % tl.bdim[1], bzz = byz / tl.bdim[1];
-            const int64_t brick = ((int64_t)(tl.blo[2] + bzz) * vd->nby + (tl.blo[1] + byy)) * vd->nbx + (tl.blo[0] + bxx);
-            const int slot = vd->table[(int64_t)sh.act_bin[k] * nbricks + brick];
-            tl.slot[e] = slot;
-            if constexpr (DT == DARE_FP8_E4M3) tl.scale[e] = slot >= 0 ? vd->scales[slot] : make_float2(0.0f, 0.0f);
+    for (int base = 0; base < nvox; base += U * NT) {
+        int row[U], loc[U], vi[U];
+        bool ok[U];
+        float A[U], B[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = base + u * NT + (int)threadIdx.x;
+            const uint32_t ent = (uint32_t)list[min(i, nvox - 1) >> 3];
+            const int x = 2 * (int)((ent >> 15) & 31) + off[0], y = 2 * (int)((ent >> 20) & 31) + off[1],
+                      z = 2 * (int)(ent >> 25) + off[2];
+            ok[u] = i < nvox && (unsigned)(x - r0[0]) < (unsigned)rn[0] && (unsigned)(y - r0[1]) < (unsigned)rn[1] &&
+                    (unsigned)(z - r0[2]) < (unsigned)rn[2];
+            vi[u] = x * str[0] + y * str[1] + z * str[2];
+            row[u] = (int)__umul24((ent >> 6) & 511, (uint32_t)kactp);
+            loc[u] = (int)(ent & 63) << 3 | ((int)threadIdx.x & 7);
+            A[u] = B[u] = 0.0f;
         }
-        // (b) the voxels in reach, as runs along the normal's dominant axis, compacted into a list
-        {
-            const int dax = tl.dax, pax = tl.pax, qax = tl.qax, depth = tl.depth;
-            const int nwork = tl.ncols * depth;
-            const int lo[3] = {tl.lo[0], tl.lo[1], tl.lo[2]}, dim[3] = {tl.dim[0], tl.dim[1], tl.dim[2]};
-            const float m[3] = {tl.m[0], tl.m[1], tl.m[2]}, c0[3] = {tl.c0[0], tl.c0[1], tl.c0[2]};
-            const float ua[3] = {tl.ua[0], tl.ua[1], tl.ua[2]}, va[3] = {tl.va[0], tl.va[1], tl.va[2]};
-            const float thr_n = tl.thr_n, thr_u = tl.thr_u, thr_v = tl.thr_v, len_u = tl.len_u, len_v = tl.len_v;
-            const float inv_md = tl.inv_md, half = thr_n * fabsf(inv_md);
-            for (int e = threadIdx.x; e < nwork; e += blockDim.x) {
-                const int col = e / depth, k = e - col * depth;
-                const int vp = lo[pax] + col % dim[pax], vq = lo[qax] + col / dim[pax];
-                const float centre = c0[dax] - (m[pax] * ((float)vp - c0[pax]) + m[qax] * ((float)vq - c0[qax])) * inv_md;
-                const int vdd = max((int)floorf(centre - half) + 1, lo[dax]) + k;
-                if (vdd >= lo[dax] + dim[dax]) continue;
-                const int vx = dax == 0 ? vdd : (pax == 0 ? vp : vq);
-                const int vy = dax == 1 ? vdd : (pax == 1 ? vp : vq);
-                const int vz = dax == 2 ? vdd : (pax == 2 ? vp : vq);
-                const float d0 = (float)vx - c0[0], d1 = (float)vy - c0[1], d2 = (float)vz - c0[2];
-                const float dn = m[0] * d0 + m[1] * d1 + m[2] * d2;
-                const float du = ua[0] * d0 + ua[1] * d1 + ua[2] * d2;
-                const float dv = va[0] * d0 + va[1] * d1 + va[2] * d2;
-                if (!(fabsf(dn) < thr_n && du > -thr_u && du < len_u + thr_u && dv > -thr_v && dv < len_v + thr_v))
-                    continue;
-                const int idx = atomicAdd(&tl.nlist, 1);
-                tl.list[idx] = (unsigned short)(((vz - lo[2]) * dim[1] + (vy - lo[1])) * dim[0] + (vx - lo[0]));
+        for (int k0 = 0; k0 < kact; k0 += NB) {
+            int sl[U][NB];
+            T pr[U][NB];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int g = 0; g < NB; g += 4) {
+                    const int4 s4 = *reinterpret_cast<const int4*>(&L.slot[row[u] + k0 + g]);
+                    sl[u][g] = s4.x;
+                    sl[u][g + 1] = s4.y;
+                    sl[u][g + 2] = s4.z;
+                    sl[u][g + 3] = s4.w;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int g = 0; g < NB; ++g) {
+                    pr[u][g] = T{};
+                    if ((uint32_t)sl[u][g] < cap) pr[u][g] = *(const T*)&data[((size_t)sl[u][g] << 9) | (uint32_t)loc[u]];
+                }
+#pragma unroll
+            for (int g = 0; g < NB; ++g) {
+                const float w = uf(L.sh.act_w[k0 + g]);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float2 sc = make_float2(0.0f, 0.0f);
+                    if constexpr (DT == DARE_FP8_E4M3) sc = L.scale[row[u] + k0 + g];
+                    float a, c;
+                    PT::decode(pr[u][g], sc, a, c);
+                    const float wc = w * c;
+                    A[u] = __builtin_fmaf(wc, a, A[u]);
+                    B[u] = B[u] + wc;
+                }
             }
         }
-        __syncthreads();
-        // (c) one thread per listed voxel: its direction blend into LDS
-        const typename Pair<DT>::T* __restrict__ data = (const typename Pair<DT>::T*)vd->data;
-        const int nlist = tl.nlist;
-        const int dxb = tl.dim[0], dyb = tl.dim[1];
-        const int lox = tl.lo[0], loy = tl.lo[1], loz = tl.lo[2];
-        const int bx0 = tl.blo[0], by0 = tl.blo[1], bz0 = tl.blo[2], bdx = tl.bdim[0], bdy = tl.bdim[1];
-        for (int e = threadIdx.x; e < nlist; e += blockDim.x) {
-            const int bi = tl.list[e];
-            const int ex = bi % dxb, eyz = bi / dxb;
-            const int vx = lox + ex, vy = loy + eyz % dyb, vz = loz + eyz / dyb;
-            const int bb = (((vz >> 3) - bz0) * bdy + ((vy >> 3) - by0)) * bdx + ((vx >> 3) - bx0);
-            const int local = brick_local(vx, vy, vz);
-            tl.V[bi] = blend_voxel_r<DT, R>(data, sh, tl, kact, bb, local);
-        }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) V[vi[u]] = B[u] > 0.0f ? A[u] / B[u] : __builtin_nanf("");
     }
-    const int i = i0 + (threadIdx.x & (kTile - 1));
-    const int j = j0 + (threadIdx.x >> 4);
-    if (i >= s.W || j >= s.H) return;
-    float* out = s.out + (size_t)j * s.W + i;
-    if (mode == 0) {
-        *out = __builtin_nanf("");
+}
+
+// Four neighbouring lattice points of one axis: 2R - 1 taps R - |k - (R - 1)| each, from the
+// 2R + 2 inputs that `in(j, x, c)` gives (numerator x, denominator c), added in order of j.
+template <int R, class In>
+__device__ __forceinline__ void taps4(In&& in, float2 (&o)[4]) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) o[b] = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int j = 0; j < 2 * R + 2; ++j) {
+        float x, c;
+        in(j, x, c);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int k = j - b;
+            if (k < 0 || k > 2 * R - 2) continue;
+            const float w = (float)(R - (k > R - 1 ? k - (R - 1) : R - 1 - k));
+            o[b].x = __builtin_fmaf(w, x, o[b].x);
+            o[b].y = __builtin_fmaf(w, c, o[b].y);
+        }
+    }
+}
+
+// The pixels of a piece from the lattice sums P3[q][p][d].
+template <int DT, int R, int DAX, int NT>
+__device__ __forceinline__ void pixels_wide(const VolView& vv, const SlicePos& q, const SliceArgs& s, const Piece& t,
+                                            int edge, const float2* P3) {
+    constexpr int PAX = DAX == 0 ? 1 : 0, QAX = DAX == 2 ? 1 : 2;
+    const int ld = t.len[DAX], lp = t.len[PAX];
+    const int shift = __builtin_ctz(edge);
+    const gptr<float> out = global(s.out);
+    for (int idx = (int)threadIdx.x; idx < edge * edge; idx += NT) {
+        const int li = idx & (edge - 1), lj = idx >> shift;
+        if (li >= t.ni || lj >= t.nj) continue;
+        const int i = t.i0 + li, j = t.j0 + lj;
+        double c[3];
+        pixel_coords(q, i, j, c);
+        float val = __builtin_nanf("");
+        if (c[0] > -(double)R && c[0] < (double)(vv.n[0] - 1 + R) && c[1] > -(double)R &&
+            c[1] < (double)(vv.n[1] - 1 + R) && c[2] > -(double)R && c[2] < (double)(vv.n[2] - 1 + R)) {
+            // per axis: the nearer corner (base) and the weight w <= 1/2 of the other one, from FP64
+            // (w is positive where FP64's is).  lerp(base, other) = base + w (other - base) is then
+            // positive whenever a corner with positive weight is, and loses nothing where both
+            // corners hold the same (D away from the borders).
+            int b[3], step[3];
+            float w[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double fl = floor(c[a]), f = c[a] - fl;
+                const bool up = f > 0.5;
+                // the cell lies in the box; the clamp only keeps the LDS reads in bounds
+                b[a] = min(max((int)fl - t.lat[a], 0), t.len[a] - 2) + (up ? 1 : 0);
+                step[a] = up ? -1 : 1;
+                w[a] = (float)(up ? fl + 1.0 - c[a] : f);
+            }
+            const float2* cell = P3 + (b[QAX] * lp + b[PAX]) * ld + b[DAX];
+            const int sd = step[DAX], sp = step[PAX] * ld, sq = step[QAX] * lp * ld;
+            auto lerp = [](float2 lo, float2 hi, float x) {
+                return make_float2(__builtin_fmaf(x, hi.x - lo.x, lo.x), __builtin_fmaf(x, hi.y - lo.y, lo.y));
+            };
+            float2 r[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float2* e = cell + (k >> 1) * sq + (k & 1) * sp;
+                r[k] = lerp(e[0], e[sd], w[DAX]);
+            }
+            const float2 nd = lerp(lerp(r[0], r[1], w[PAX]), lerp(r[2], r[3], w[PAX]), w[QAX]);
+            if (nd.y > 0.0f) val = nd.x / nd.y;
+        }
+        out[(size_t)j * s.W + i] = val;
+    }
+}
+
+// A piece with nothing in reach, or of a request with no surviving bin: NaN.
+template <int NT>
+__device__ __forceinline__ void nan_piece(const SliceArgs& s, int i0, int j0, int ni, int nj) {
+    const gptr<float> out = global(s.out);
+    for (int idx = (int)threadIdx.x; idx < 256; idx += NT) {
+        const int li = idx & 15, lj = idx >> 4;
+        if (li < ni && lj < nj) out[(size_t)(j0 + lj) * s.W + (i0 + li)] = __builtin_nanf("");
+    }
+}
+
+// One staged piece of a tile (edge x edge pixels at most), `t`'s pixels, lattice and c0 set.
+template <int DT, int R, int NT>
+__device__ __forceinline__ void wide_piece(const VolView& vv, const SlicePos& q, const SliceArgs& s, Piece& t,
+                                           int edge, int dax, int kact, int kactp, WideLds<DT, R>& L) {
+    const int tid = (int)threadIdx.x;
+    bool empty = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        t.lo[a] = t.lat[a] - (R - 1);
+        t.dim[a] = t.len[a] + 2 * R - 2;
+        const int lo = max(t.lo[a], 0), hi = min(t.lo[a] + t.dim[a], vv.n[a]) - 1;
+        t.blo[a] = lo >> 3;
+        t.bdim[a] = (hi >> 3) - t.blo[a] + 1;
+        empty = empty || lo > hi;
+    }
+    if (empty) {
+        nan_piece<NT>(s, t.i0, t.j0, t.ni, t.nj);
+        return;
+    }
+    const int pax = dax == 0 ? 1 : 0, qax = dax == 2 ? 1 : 2;
+    const int vd = pick3(t.dim, dax), vp = pick3(t.dim, pax), vq = pick3(t.dim, qax);
+    const int ld = pick3(t.len, dax), lp = pick3(t.len, pax), lq = pick3(t.len, qax);
+    const int nv = vd * vp * vq;
+    float* V = L.pool;
+    float2* P2 = reinterpret_cast<float2*>(L.pool);
+    float* side = L.pool + ((max(nv, 2 * ld * lp * vq) + 3) & ~3);
+    int* list = reinterpret_cast<int*>(side);
+    float2* P1 = reinterpret_cast<float2*>(side);
+    // slots: the table entry of every (box brick, bin) pair, -1 past the surviving bins; a thread's
+    // first read is in flight during the classification
+    const int nsl = t.bdim[0] * t.bdim[1] * t.bdim[2] * kactp;
+    const SmallDiv dk = small_div(kactp), dx = small_div(t.bdim[0]), dy = small_div(t.bdim[1]);
+    auto slot_of = [&](int e) {
+        const int bb = sdiv(e, dk), k = e - bb * kactp;
+        if (e >= nsl || k >= kact) return -1;
+        const int byz = sdiv(bb, dx), bx = bb - byz * t.bdim[0];
+        const int bz = sdiv(byz, dy), by = byz - bz * t.bdim[1];
+        const int64_t brick = ((int64_t)(t.blo[2] + bz) * vv.nby + (t.blo[1] + by)) * vv.nbx + (t.blo[0] + bx);
+        return (int)global(vv.table)[(int64_t)L.sh.act_bin[k] * vv.nbricks + brick];
+    };
+    auto put_slot = [&](int e, int slot) {
+        if (e >= nsl) return;
+        L.slot[e] = slot;
+        if constexpr (DT == DARE_FP8_E4M3) L.scale[e] = slot >= 0 ? vv.scales[slot] : make_float2(0.0f, 0.0f);
+    };
+    const int slot0 = slot_of(tid);
+    {   // every voxel starts NaN; the gather overwrites those it reaches
+        const float nan = __builtin_nanf("");
+        for (int e = 4 * tid; e < nv; e += 4 * NT) *reinterpret_cast<float4*>(&V[e]) = make_float4(nan, nan, nan, nan);
+    }
+    if (tid == 0) L.nlist = 0;
+    __syncthreads();
+    list_cubes<DT, R, NT>(vv, t, L, list);
+    put_slot(tid, slot0);
+    for (int e = tid + NT; e < nsl; e += NT) put_slot(e, slot_of(e));
+    __syncthreads();
+    gather_wide<DT, R, NT>(vv, t, dax, L, list, V, kact, kactp);
+    __syncthreads();
+    {   // along d: V -> P1[q][p][g]
+        const int nb = (ld + 3) >> 2, n = vp * vq * nb;
+        const SmallDiv db = small_div(nb);
+        for (int x = tid; x < n; x += NT) {
+            const int col = sdiv(x, db), b = x - col * nb, base = col * vd + 4 * b, left = vd - 1 - 4 * b;
+            float2 o[4];
+            taps4<R>([&](int j, float& num, float& den) {
+                const float v = V[base + min(j, left)];
+                const bool ok = v == v;
+                num = ok ? v : 0.0f;
+                den = ok ? 1.0f : 0.0f;
+            }, o);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (4 * b + k < ld) P1[col * ld + 4 * b + k] = o[k];
+        }
+    }
+    __syncthreads();
+    {   // along p: P1 -> P2[q][gp][g]
+        const int nb = (lp + 3) >> 2, n = vq * nb * ld;
+        const SmallDiv dl = small_div(ld), db = small_div(nb);
+        for (int x = tid; x < n; x += NT) {
+            const int r = sdiv(x, dl), g = x - r * ld, cq = sdiv(r, db), b = r - cq * nb;
+            const int base = (cq * vp + 4 * b) * ld + g, left = vp - 1 - 4 * b;
+            float2 o[4];
+            taps4<R>([&](int j, float& num, float& den) {
+                const float2 v = P1[base + min(j, left) * ld];
+                num = v.x;
+                den = v.y;
+            }, o);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (4 * b + k < lp) P2[(cq * lp + 4 * b + k) * ld + g] = o[k];
+        }
+    }
+    __syncthreads();
+    {   // along q: P2 -> P3[gq][gp][g], in P1's place
+        const int nb = (lq + 3) >> 2, plane = lp * ld, n = nb * plane;
+        const SmallDiv dp = small_div(plane);
+        for (int x = tid; x < n; x += NT) {
+            const int b = sdiv(x, dp), g = x - b * plane, base = 4 * b * plane + g, left = vq - 1 - 4 * b;
+            float2 o[4];
+            taps4<R>([&](int j, float& num, float& den) {
+                const float2 v = P2[base + min(j, left) * plane];
+                num = v.x;
+                den = v.y;
+            }, o);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (4 * b + k < lq) P1[base + k * plane] = o[k];
+        }
+    }
+    __syncthreads();
+    switch (dax) {
+        case 0: pixels_wide<DT, R, 0, NT>(vv, q, s, t, edge, P1); break;
+        case 1: pixels_wide<DT, R, 1, NT>(vv, q, s, t, edge, P1); break;
+        default: pixels_wide<DT, R, 2, NT>(vv, q, s, t, edge, P1); break;
+    }
+}
+
+// One 16 x 16 tile at radius R.
+template <int DT, int R, int NT>
+__device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const SliceArgs& s, int unit,
+                                          WideLds<DT, R>& L) {
+    const int ty = unit / s.tiles_x, tx = unit - ty * s.tiles_x;
+    const int i0 = tx * kTile, j0 = ty * kTile;
+    {   // the bins on wave 0 and the plane's frame on wave 1, at once
+        double T[12];
+        if (threadIdx.x < 64) {
+            pad_bins(L.sh, slice_gates(vd, s, L.sh, T));
+        } else if (threadIdx.x < 128) {
+            slice_pose(vd, s, T);
+            if (threadIdx.x == 64) slice_frame(vd, s, T, L.sh);
+        }
+    }
+    __syncthreads();
+    const int kact = ui(L.sh.kact), kactp = (kact + 7) & ~7, dax = ui(L.sh.dax);
+    if (kact == 0) {
+        nan_piece<NT>(s, i0, j0, min(kTile, s.W - i0), min(kTile, s.H - j0));
         return;
     }
     SlicePos q;
-    load_pos(vd, sh, s, q);
-    const int n[3] = {vd->nx, vd->ny, vd->nz};
-    double c[3];
-    pixel_coords(q, i, j, c);
-    if (!(c[0] > -(double)R && c[0] < (double)(n[0] - 1 + R) && c[1] > -(double)R && c[1] < (double)(n[1] - 1 + R) &&
-          c[2] > -(double)R && c[2] < (double)(n[2] - 1 + R))) {
-        *out = __builtin_nanf("");
+    load_pos(vd, L.sh, s, q);
+    const VolView vv = view_of(vd);
+    Piece t;
+    t.i0 = i0;
+    t.j0 = j0;
+    t.ni = min(kTile, s.W - i0);
+    t.nj = min(kTile, s.H - j0);
+    tile_cells(q, i0, j0, i0 + t.ni - 1, j0 + t.nj - 1, t.lat, t.len, t.c0);
+    if (wide_fits<R>(t.len, dax, kactp)) {
+        wide_piece<DT, R, NT>(vv, q, s, t, kTile, dax, kact, kactp, L);
         return;
     }
-    const double f0 = floor(c[0]), f1 = floor(c[1]), f2 = floor(c[2]);
-    const int b0[3] = {(int)f0, (int)f1, (int)f2};
-    const float fr[3] = {(float)(c[0] - f0), (float)(c[1] - f1), (float)(c[2] - f2)};
-    const float gr[3] = {(float)(f0 + 1.0 - c[0]), (float)(f1 + 1.0 - c[1]), (float)(f2 + 1.0 - c[2])};
-    const float invR = 1.0f / (float)R;
-    // tent weights per axis for offsets -R+1 .. R
-    float tw[3][2 * R];
+    // the largest piece whose box fits wherever it falls: a piece's cells span at most its
+    // extent's floor plus one, hence that plus three lattice points; one pixel has two
+    int edge = kTile / 2;
+    for (; edge > 1; edge >>= 1) {
+        int len[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int o = 0; o < 2 * R; ++o) tw[a][o] = tent_weight(o - R + 1, fr[a], gr[a], R, invR);
-    float num = 0.0f, den = 0.0f;
-    if (mode == 2) {
-        for (int oz = 0; oz < 2 * R; ++oz)
-            for (int oy = 0; oy < 2 * R; ++oy)
-#pragma unroll
-                for (int ox = 0; ox < 2 * R; ++ox) {
-                    const int vx = b0[0] + ox - R + 1, vy = b0[1] + oy - R + 1, vz = b0[2] + oz - R + 1;
-                    const float t = (tw[0][ox] * tw[1][oy]) * tw[2][oz];
-                    if (!(t > 0.0f) || (unsigned)vx >= (unsigned)n[0] || (unsigned)vy >= (unsigned)n[1] ||
-                        (unsigned)vz >= (unsigned)n[2])
-                        continue;
-                    const float V = voxel_value<DT>(vd, sh, kact, vx, vy, vz);
-                    if (V == V) {
-                        num = __builtin_fmaf(t, V, num);
-                        den = den + t;
-                    }
-                }
-    } else {
-        // every in-grid voxel with weight was staged; voxels outside the box are outside the grid
-        const int dx = tl.dim[0], dy = tl.dim[1], dz = tl.dim[2];
-        const int ex0 = b0[0] - R + 1 - tl.lo[0], ey0 = b0[1] - R + 1 - tl.lo[1], ez0 = b0[2] - R + 1 - tl.lo[2];
-        for (int oz = 0; oz < 2 * R; ++oz) {
-            const int ez = ez0 + oz;
-            for (int oy = 0; oy < 2 * R; ++oy) {
-                const int ey = ey0 + oy;
-                const bool row_in = (unsigned)ez < (unsigned)dz && (unsigned)ey < (unsigned)dy;
-                const float tyz = tw[1][oy] * tw[2][oz];
-                const int rowb = (ez * dy + ey) * dx;
-#pragma unroll
-                for (int ox = 0; ox < 2 * R; ++ox) {
-                    const int ex = ex0 + ox;
-                    const float t = tw[0][ox] * tyz;
-                    const bool ok = row_in && (unsigned)ex < (unsigned)dx && t > 0.0f;
-                    const float V = tl.V[ok ? rowb + ex : 0];
-                    if (ok && V == V) {
-                        num = __builtin_fmaf(t, V, num);
-                        den = den + t;
-                    }
-                }
-            }
+        for (int a = 0; a < 3; ++a) {
+            const double ext = (double)(edge - 1) * (fabs(q.sx * q.e0[a]) + fabs(q.sy * q.e1[a])) * q.inv_h;
+            len[a] = ui((int)fmin(ext * (1.0 + 1e-9) + 1e-6, 1024.0) + 3);
         }
+        if (wide_fits<R>(len, dax, kactp)) break;
     }
-    *out = den > 0.0f ? num / den : __builtin_nanf("");
+    for (int y = 0; y < t.nj; y += edge)
+        for (int x = 0; x < t.ni; x += edge) {
+            Piece u;
+            u.i0 = i0 + x;
+            u.j0 = j0 + y;
+            u.ni = min(edge, t.ni - x);
+            u.nj = min(edge, t.nj - y);
+            tile_cells(q, u.i0, u.j0, u.i0 + u.ni - 1, u.j0 + u.nj - 1, u.lat, u.len, u.c0);
+            wide_piece<DT, R, NT>(vv, q, s, u, edge, dax, kact, kactp, L);
+            __syncthreads();
+        }
 }
 
 }  // namespace
 
 template <int DT, int R>
-__global__ void __launch_bounds__(256) k_reslice_rs(const VolDev* __restrict__ vd, SliceArgs s) {
-    __shared__ SetupLds sh;
-    __shared__ TileLdsR<DT, R> tl;
-    reslice_tile_rs<DT, R>(vd, s, xcd_remap(blockIdx.x, gridDim.x), sh, tl);
+__global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs(const VolDev* __restrict__ vd, SliceArgs s) {
+    __shared__ WideLds<DT, R> L;
+    wide_tile<DT, R, WideLimits<R>::kThreads>(vd, s, xcd_remap(blockIdx.x, gridDim.x), L);
 }
 
 // Batched form: (request, tile) units, grid-stride; every tile computes its own setup, so a
 // request's result is the one it gets alone.
 template <int DT, int R>
-__global__ void __launch_bounds__(256) k_reslice_rs_batch(const BatchReq* __restrict__ reqs,
-                                                          const int2* __restrict__ units,
-                                                          const int* __restrict__ counts) {
-    __shared__ SetupLds sh;
-    __shared__ TileLdsR<DT, R> tl;
+__global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs_batch(const BatchReq* __restrict__ reqs,
+                                                                              const int2* __restrict__ units,
+                                                                              const int* __restrict__ counts) {
+    __shared__ WideLds<DT, R> L;
     const int nunits = counts[0];
     for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
-        const int r = __builtin_amdgcn_readfirstlane(units[u].x);
-        const int t = __builtin_amdgcn_readfirstlane(units[u].y);
-        reslice_tile_rs<DT, R>(reqs[r].vol, reqs[r].s, t, sh, tl);
+        const int r = ui(units[u].x), t = ui(units[u].y);
+        wide_tile<DT, R, WideLimits<R>::kThreads>(reqs[r].vol, reqs[r].s, t, L);
         __syncthreads();
     }
 }
 
 int64_t staged_tiles(int W, int H) { return (int64_t)((W + kTile - 1) / kTile) * ((H + kTile - 1) / kTile); }
 
-hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, hipStream_t stream) {
-    const dim3 grid((unsigned)staged_tiles(s.W, s.H)), block(256);
-#define S2(D) hipLaunchKernelGGL((k_reslice_rs<D, 2>), grid, block, 0, stream, vd, s)
-#define S3(D) hipLaunchKernelGGL((k_reslice_rs<D, 3>), grid, block, 0, stream, vd, s)
-#define S4(D) hipLaunchKernelGGL((k_reslice_rs<D, 4>), grid, block, 0, stream, vd, s)
-    switch (radius) {
-        case 2: DARE_DISPATCH_DT(dtype, S2) break;
-        case 3: DARE_DISPATCH_DT(dtype, S3) break;
-        case 4: DARE_DISPATCH_DT(dtype, S4) break;
-        default: return hipErrorInvalidValue;
+#define DARE_DISPATCH_R(radius, MACRO)                          \
+    switch (radius) {                                           \
+        case 2: MACRO(2); break;                                \
+        case 3: MACRO(3); break;                                \
+        case 4: MACRO(4); break;                                \
+        case 5: MACRO(5); break;                                \
+        case 6: MACRO(6); break;                                \
+        case 7: MACRO(7); break;                                \
+        case 8: MACRO(8); break;                                \
+        default: return hipErrorInvalidValue;                   \
     }
-#undef S2
-#undef S3
-#undef S4
+
+template <int DT>
+static hipError_t launch_one(const VolDev* vd, int radius, const SliceArgs& s, hipStream_t stream) {
+    const dim3 grid((unsigned)staged_tiles(s.W, s.H));
+#define S(R) hipLaunchKernelGGL((k_reslice_rs<DT, R>), grid, dim3(WideLimits<R>::kThreads), 0, stream, vd, s)
+    DARE_DISPATCH_R(radius, S)
+#undef S
     return hipGetLastError();
+}
+
+template <int DT>
+static hipError_t launch_many(int radius, const BatchReq* reqs, const int2* units, const int* counts, int grid,
+                              hipStream_t stream) {
+#define B(R)                                                                                                       \
+    hipLaunchKernelGGL((k_reslice_rs_batch<DT, R>), dim3(grid), dim3(WideLimits<R>::kThreads), 0, stream, reqs,   \
+                       units, counts)
+    DARE_DISPATCH_R(radius, B)
+#undef B
+    return hipGetLastError();
+}
+
+hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, hipStream_t stream) {
+#define L(D) return launch_one<D>(vd, radius, s, stream)
+    DARE_DISPATCH_DT(dtype, L)
+#undef L
 }
 
 hipError_t launch_reslice_staged_batch(int dtype, int radius, const BatchReq* reqs, const int2* units,
                                        const int* counts, int grid, hipStream_t stream) {
-#define B2(D) hipLaunchKernelGGL((k_reslice_rs_batch<D, 2>), dim3(grid), dim3(256), 0, stream, reqs, units, counts)
-#define B3(D) hipLaunchKernelGGL((k_reslice_rs_batch<D, 3>), dim3(grid), dim3(256), 0, stream, reqs, units, counts)
-#define B4(D) hipLaunchKernelGGL((k_reslice_rs_batch<D, 4>), dim3(grid), dim3(256), 0, stream, reqs, units, counts)
-    switch (radius) {
-        case 2: DARE_DISPATCH_DT(dtype, B2) break;
-        case 3: DARE_DISPATCH_DT(dtype, B3) break;
-        case 4: DARE_DISPATCH_DT(dtype, B4) break;
-        default: return hipErrorInvalidValue;
-    }
-#undef B2
-#undef B3
-#undef B4
-    return hipGetLastError();
+#define L(D) return launch_many<D>(radius, reqs, units, counts, grid, stream)
+    DARE_DISPATCH_DT(dtype, L)
+#undef L
 }
 
+// The unit entries a workspace holds for a request.  Above radius 4 that is one for 4 pixels, more
+// than its tiles: what a workspace must hold, and so which batches a given one admits, is part of
+// what callers have sized for.
 int64_t batch_units(int radius, int W, int H) {
-    return staged_radius(radius) ? staged_tiles(W, H) : reslice_units(radius, W, H);
+    return radius <= 4 ? staged_tiles(W, H) : ((int64_t)W * H + 3) / 4;
 }
 
 }  // namespace dare

@@ -38,7 +38,6 @@ int volume_dtype(const dare_volume* v);
 int volume_radius(const dare_volume* v);
 int volume_device_id(const dare_volume* v);
 uint64_t volume_arena_size(const dare_volume* v);
-int reslice_lanes(int radius);
 dare_status check_slice_spec(const dare_slice_spec* s);
 }  // namespace dare
 
@@ -54,7 +53,7 @@ double now_s() {
     return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
-// Work units of a request (radius 1: the most the device may append, 16 x 16 tiles).
+// Unit entries of a request (radius 1: the most the device may append, 16 x 16 tiles).
 int64_t units_of(int radius, int W, int H) {
     return radius <= 1 ? tile_units_max(W, H) : batch_units(radius, W, H);
 }
@@ -302,7 +301,8 @@ bool launch_tick(dare_server* S, Slot& sl) {
         q.s.out = (float*)(S->arena + off);
         breqs.push_back(q);
         if (host_units)
-            for (int64_t t = 0; t < r.units; ++t) bunits.push_back(make_int2(nreq, (int)t));
+            for (int64_t t = 0, nt = staged_tiles(r.spec.width, r.spec.height); t < nt; ++t)
+                bunits.push_back(make_int2(nreq, (int)t));
         sl.tickets.push_back(S->queue.front());
         S->queue.pop_front();
         pixels += px;
@@ -311,7 +311,7 @@ bool launch_tick(dare_server* S, Slot& sl) {
     }
     if (nreq == 0) return false;
     BatchHeader hd{};
-    hd.counts[0] = host_units ? (int)units : 0;   // radius 1: the setup pass appends the units
+    hd.counts[0] = host_units ? (int)bunits.size() : 0;   // radius 1: the setup pass appends the units
     hd.counts[1] = nreq;
     memcpy(sl.staging, &hd, sizeof(hd));
     memcpy(sl.staging + S->o_req, breqs.data(), breqs.size() * sizeof(BatchReq));
@@ -424,9 +424,9 @@ bool volume_open(const dare_server* S, int32_t id) {
 // request table, unit table (sized for a full tick at this radius) and setup records.
 dare_status layout_workspaces(dare_server* S, int radius) {
     const dare_server_config& c = S->cfg;
-    // pixels per unit: 16 x 16 tiles up to radius 4, 256 / (lanes per pixel) beyond; a request
+    // pixels per unit entry (batch_units): 16 x 16 tiles up to radius 4, 4 pixels beyond; a request
     // adds at most one partial tile per row and column of tiles
-    const int64_t ppu = radius <= 4 ? 256 : 256 / reslice_lanes(radius);
+    const int64_t ppu = radius <= 4 ? 256 : 4;
     int64_t mu = c.max_tick_pixels / ppu + (radius <= 4 ? 300 : 1) * (int64_t)c.max_tick_requests;
     S->max_units = std::min<int64_t>(mu, (int64_t)1 << 28);
     S->o_req = aup(sizeof(BatchHeader));

@@ -1,18 +1,18 @@
-// Reslice at interpolation radius 2..4 with per-tile LDS staging of the voxel direction
-// blends (dare_reslice_rs.hip).  Other radii use the per-pixel kernels of dare_reslice.hip.
+// Reslice at interpolation radius 2..8 through the tent sums of the voxel lattice
+// (dare_reslice_rs.hip).  Radius 1 runs the tile kernels of dare_tiles.hip.
 #pragma once
 
 #include "dare_batch.h"
 
 namespace dare {
 
-inline bool staged_radius(int radius) { return radius >= 2 && radius <= 4; }
-
 hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, hipStream_t stream);
 // Batched form over (request, tile) units; counts[0] holds the number of units.
 hipError_t launch_reslice_staged_batch(int dtype, int radius, const BatchReq* reqs, const int2* units,
                                        const int* counts, int grid, hipStream_t stream);
-// Work units of a W x H request at this radius for the batched kernels (tiles when staged).
+// Work units of a W x H request: its 16 x 16 tiles.
+int64_t staged_tiles(int W, int H);
+// Unit entries that a workspace holds for a W x H request at this radius (at least its tiles).
 int64_t batch_units(int radius, int W, int H);
 
 }  // namespace dare

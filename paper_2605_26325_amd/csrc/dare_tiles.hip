@@ -74,33 +74,12 @@ struct TileLds {
     int nlist;
 };
 
-// Pointers in the global address space, so that loads and stores through them are global (not
-// flat) operations, whose waits do not wait for LDS and vice versa.
-template <class T>
-using gptr = __attribute__((address_space(1))) T*;
-template <class T>
-__device__ __forceinline__ gptr<T> global(T* p) {
-    return (gptr<T>)(p);
-}
-
-// Workgroup-uniform values, moved to scalar registers.
-__device__ __forceinline__ int ui(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ float uf(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
-__device__ __forceinline__ double ud(double x) { return uniform_f64(x); }
-__device__ __forceinline__ SmallDiv usd(uint32_t m, int d) { return SmallDiv{(uint32_t)ui((int)m), ui(d)}; }
-
 // Upper bound of a tile's box edge along one axis (T pixels per side): the corner cells'
 // floors differ by at most ceil of the tile's extent, and the box adds one voxel below and two
 // above (the upper cell voxel and a margin for rounding).
 __device__ __forceinline__ int box_edge_bound(int T, double ex, double ey) {
     const double ext = (double)(T - 1) * (fabs(ex) + fabs(ey));
     return (int)floor(ext * (1.0 + 1e-9) + 1e-6) + 5;
-}
-
-// Entry i of a 3-vector held in registers, without indexing it (which would put it in memory).
-template <class T>
-__device__ __forceinline__ T pick3(const T (&v)[3], int i) {
-    return i == 0 ? v[0] : (i == 1 ? v[1] : v[2]);
 }
 
 // What a tile record needs of its request, held in registers by the thread that writes it.
@@ -214,15 +193,6 @@ __device__ __forceinline__ int request_mode(Plane& pl, SliceRec& rec, int max_ti
     rec.tiles_x = pl.tiles_x;
     rec.ntiles = pl.tiles_x * ((pl.H + tile - 1) / tile);
     return mode;
-}
-
-// Bins past the survivors: no slots, zero weight (one wave, lane b for bin b).
-__device__ __forceinline__ void pad_bins(SliceRec& rec, int kact) {
-    const int lane = threadIdx.x & 63;
-    if (lane >= kact) {
-        rec.act_bin[lane] = 0;
-        rec.act_w[lane] = 0.0f;
-    }
 }
 
 // One wave: the per-request setup of a radius-1 reslice, in FP64 on the device, into `rec`.
@@ -423,33 +393,6 @@ __device__ __forceinline__ float unfold(float q) {
     else if constexpr (DT == DARE_FP8_E4M3) return q + 127.5f;
     else return q * 127.5f + 127.5f;
 }
-
-// First voxel of the run of column (vp, vq): the first whole voxel above centre - half, where
-// centre is the plane's coordinate along DAX at the column (FP32 about the tile's origin c0).
-// The column's voxels with |m.(v - c0)| < thr_n are among the depth voxels from there.
-template <int DAX>
-__device__ __forceinline__ int run_start(const float (&c0)[3], const float (&m)[3], float inv_md, float half, int vp,
-                                         int vq) {
-    constexpr int PAX = DAX == 0 ? 1 : 0, QAX = DAX == 2 ? 1 : 2;
-    const float centre = c0[DAX] - (m[PAX] * ((float)vp - c0[PAX]) + m[QAX] * ((float)vq - c0[QAX])) * inv_md;
-    return (int)floorf(centre - half) + 1;
-}
-
-// The bits that voxel coordinate v along axis A contributes to its brick-local index: the index
-// interleaves the coordinates' bits, so it is the sum (an OR of disjoint fields) of one part per
-// axis, and a list entry can add the dominant axis's part to a per-column remainder.
-template <int A>
-__host__ __device__ constexpr int local_part(int v) {
-    return A == 0 ? ((v & 6) << 6) | (v & 1) : (A == 1 ? ((v & 6) << 4) | ((v & 1) << 1) : (v & 7) << 2);
-}
-constexpr bool local_parts_match() {
-    for (int x = 0; x < 8; ++x)
-        for (int y = 0; y < 8; ++y)
-            for (int z = 0; z < 8; ++z)
-                if (brick_local(x, y, z) != (local_part<0>(x) | local_part<1>(y) | local_part<2>(z))) return false;
-    return true;
-}
-static_assert(local_parts_match(), "the brick-local index is the sum of its per-axis parts");
 
 // Voxels phase, first part: one thread per box column (p, q) walks the column's run along the
 // dominant axis; each voxel is tested against the tile's slab and lateral extent (the test terms
