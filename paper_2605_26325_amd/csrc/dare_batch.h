@@ -15,7 +15,7 @@ struct BatchReq {
 };
 
 // Batch header at the start of a workspace: int32 counts {units, requests, units at the list's
-// back, 0}, then the radius-1 tile kernel's claim counter of each of the 8 XCDs, each on a
+// back, workgroups per unit (radii above 1)}, then the radius-1 tile kernel's claim counter of each of the 8 XCDs, each on a
 // 256-byte line of its own (claims[x][0]: counters that share a line serialise each other's
 // atomics).  At radius 1 the units are appended on the device, so counts[0] and counts[2] must be
 // uploaded as 0, and so must the claims; at other radii the host uploads the unit list and its

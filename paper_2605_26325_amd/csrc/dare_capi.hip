@@ -162,6 +162,11 @@ int gate_bins(const dare_volume* v, const double T[16], int32_t* bins, double* w
     return n;
 }
 
+// The larger output pitch in voxels.
+double pitch_vox(const dare_volume* v, const dare_slice_spec* s) {
+    return std::max(s->pitch_mm[0], s->pitch_mm[1]) / v->g.spacing_mm;
+}
+
 SliceArgs make_args(const dare_slice_spec* s, float* out) {
     SliceArgs a{};
     memcpy(a.P, s->probe_pose, sizeof(a.P));
@@ -187,6 +192,7 @@ int volume_dtype(const dare_volume* v) { return v->dtype; }
 int volume_radius(const dare_volume* v) { return (int)v->p.radius_vox; }
 int volume_device_id(const dare_volume* v) { return v->device; }
 uint64_t volume_arena_size(const dare_volume* v) { return v->arena_bytes; }
+double volume_spacing(const dare_volume* v) { return v->g.spacing_mm; }
 dare_status check_slice_spec(const dare_slice_spec* s) { return check_spec(s); }
 bool rigid_pose(const double* M) { return rigid(M); }
 void compose_pose(const double* P, const double* C, double* T) { compose_host(P, C, T); }
@@ -199,6 +205,7 @@ namespace {
 struct Group {
     std::vector<BatchReq> reqs;
     std::vector<int2> units;      // radii above 1: built here; radius 1: built on the device
+    double pitch = 0.0;           // largest output pitch, voxels (radii above 1)
     int64_t nunits = 0;           // unit entries of the workspace (radius 1: the most the device may append)
 };
 
@@ -586,7 +593,7 @@ dare_status dare_reslice(const dare_volume* v, const dare_slice_spec* spec, floa
     DeviceGuard dg(v->device);
     const SliceArgs a = make_args(spec, out_dev);
     const int R = (int)v->p.radius_vox;
-    if (R > 1) return hip_status(launch_reslice_staged(v->dev, v->dtype, R, a, (hipStream_t)stream));
+    if (R > 1) return hip_status(launch_reslice_staged(v->dev, v->dtype, R, a, pitch_vox(v, spec), (hipStream_t)stream));
     return hip_status(launch_reslice_tile(v->dev, v->dtype, a, (hipStream_t)stream));
 }
 
@@ -642,6 +649,7 @@ dare_status run_batch(const dare_volume* const* vols, const dare_slice_spec* spe
             const int64_t u = staged_tiles(specs[k].width, specs[k].height);
             for (int64_t t = 0; t < u; ++t) g.units.push_back(make_int2(r, (int)t));
             g.nunits += batch_units(R, specs[k].width, specs[k].height);
+            g.pitch = std::max(g.pitch, pitch_vox(vols[k], specs + k));
         }
         g.reqs.push_back(q);
     }
@@ -659,12 +667,14 @@ dare_status run_batch(const dare_volume* const* vols, const dare_slice_spec* spe
         BatchHeader hd{};
         hd.counts[0] = host_units ? (int)g.units.size() : 0;
         hd.counts[1] = nreq;
+        const int parts = host_units ? staged_parts((int64_t)g.units.size(), g.pitch) : 1;
+        hd.counts[3] = host_units ? parts : 0;
         memcpy(host.data(), &hd, sizeof(hd));
         memcpy(host.data() + L.o_req, g.reqs.data(), g.reqs.size() * sizeof(BatchReq));
         if (host_units && !g.units.empty())
             memcpy(host.data() + L.o_units, g.units.data(), g.units.size() * sizeof(int2));
         if (!upload(ws, host.data(), bytes)) return DARE_ERR_HIP;
-        const int grid = R <= 1 ? kBatchGrid : (int)std::min<int64_t>((int64_t)g.units.size(), 65535);
+        const int grid = R <= 1 ? kBatchGrid : (int)std::min<int64_t>((int64_t)g.units.size() * parts, 65535);
         HIP_TRY(launch_reslice_batch(std::get<0>(kv.first), R, (const BatchReq*)(ws + L.o_req),
                                      (SliceRec*)(ws + L.o_rec), (int2*)(ws + L.o_units), (TileRec*)(ws + L.o_tiles),
                                      (int*)ws, nreq, (int)g.nunits, grid, stream));

@@ -26,6 +26,8 @@
 // One workgroup takes a 16 x 16 tile, in one piece if its voxel box fits the LDS budget and in
 // pieces of 8, 4, 2 or 1 pixels squared if not (coarse output pitch).  A single pixel's box
 // always fits.
+#include <algorithm>
+
 #include "dare_reslice_dev.h"
 #include "dare_staged.h"
 
@@ -455,10 +457,11 @@ __device__ __forceinline__ void wide_piece(const VolView& vv, const SlicePos& q,
     }
 }
 
-// One 16 x 16 tile at radius R.
+// Part `part` of `parts` of a 16 x 16 tile at radius R: the whole tile is part 0's if it fits in one
+// piece, else the parts take the pieces in turn.
 template <int DT, int R, int NT>
-__device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const SliceArgs& s, int unit,
-                                          WideLds<DT, R>& L) {
+__device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const SliceArgs& s, int unit, int part,
+                                          int parts, WideLds<DT, R>& L) {
     const int ty = unit / s.tiles_x, tx = unit - ty * s.tiles_x;
     const int i0 = tx * kTile, j0 = ty * kTile;
     {   // the bins on wave 0 and the plane's frame on wave 1, at once
@@ -473,7 +476,7 @@ __device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const S
     __syncthreads();
     const int kact = ui(L.sh.kact), kactp = (kact + 7) & ~7, dax = ui(L.sh.dax);
     if (kact == 0) {
-        nan_piece<NT>(s, i0, j0, min(kTile, s.W - i0), min(kTile, s.H - j0));
+        if (part == 0) nan_piece<NT>(s, i0, j0, min(kTile, s.W - i0), min(kTile, s.H - j0));
         return;
     }
     SlicePos q;
@@ -486,7 +489,15 @@ __device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const S
     t.nj = min(kTile, s.H - j0);
     tile_cells(q, i0, j0, i0 + t.ni - 1, j0 + t.nj - 1, t.lat, t.len, t.c0);
     if (wide_fits<R>(t.len, dax, kactp)) {
-        wide_piece<DT, R, NT>(vv, q, s, t, kTile, dax, kact, kactp, L);
+        if (part == 0) wide_piece<DT, R, NT>(vv, q, s, t, kTile, dax, kact, kactp, L);
+        return;
+    }
+    // a tile out of reach of the grid as a whole (a view much larger than the volume)
+    bool out = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out = out || t.lat[a] - (R - 1) >= vv.n[a] || t.lat[a] + t.len[a] + R - 2 < 0;
+    if (out) {
+        if (part == 0) nan_piece<NT>(s, i0, j0, t.ni, t.nj);
         return;
     }
     // the largest piece whose box fits wherever it falls: a piece's cells span at most its
@@ -501,38 +512,44 @@ __device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const S
         }
         if (wide_fits<R>(len, dax, kactp)) break;
     }
-    for (int y = 0; y < t.nj; y += edge)
-        for (int x = 0; x < t.ni; x += edge) {
-            Piece u;
-            u.i0 = i0 + x;
-            u.j0 = j0 + y;
-            u.ni = min(edge, t.ni - x);
-            u.nj = min(edge, t.nj - y);
-            tile_cells(q, u.i0, u.j0, u.i0 + u.ni - 1, u.j0 + u.nj - 1, u.lat, u.len, u.c0);
-            wide_piece<DT, R, NT>(vv, q, s, u, edge, dax, kact, kactp, L);
-            __syncthreads();
-        }
+    const int shift = __builtin_ctz(kTile / edge), across = 1 << shift;
+    for (int k = part; k < across * across; k += parts) {
+        const int x = (k & (across - 1)) * edge, y = (k >> shift) * edge;
+        if (x >= t.ni || y >= t.nj) continue;
+        Piece u;
+        u.i0 = i0 + x;
+        u.j0 = j0 + y;
+        u.ni = min(edge, t.ni - x);
+        u.nj = min(edge, t.nj - y);
+        tile_cells(q, u.i0, u.j0, u.i0 + u.ni - 1, u.j0 + u.nj - 1, u.lat, u.len, u.c0);
+        wide_piece<DT, R, NT>(vv, q, s, u, edge, dax, kact, kactp, L);
+        __syncthreads();
+    }
 }
 
 }  // namespace
 
 template <int DT, int R>
-__global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs(const VolDev* __restrict__ vd, SliceArgs s) {
+__global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs(const VolDev* __restrict__ vd, SliceArgs s,
+                                                                        int parts) {
     __shared__ WideLds<DT, R> L;
-    wide_tile<DT, R, WideLimits<R>::kThreads>(vd, s, xcd_remap(blockIdx.x, gridDim.x), L);
+    const int b = xcd_remap(blockIdx.x, gridDim.x), unit = b / parts;
+    wide_tile<DT, R, WideLimits<R>::kThreads>(vd, s, unit, b - unit * parts, parts, L);
 }
 
-// Batched form: (request, tile) units, grid-stride; every tile computes its own setup, so a
-// request's result is the one it gets alone.
+// Batched form: (request, tile) units times parts, grid-stride; every tile computes its own setup,
+// so a request's result is the one it gets alone.
 template <int DT, int R>
 __global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs_batch(const BatchReq* __restrict__ reqs,
                                                                               const int2* __restrict__ units,
                                                                               const int* __restrict__ counts) {
     __shared__ WideLds<DT, R> L;
-    const int nunits = counts[0];
-    for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
+    const int parts = max(counts[3], 1);
+    const int64_t n = (int64_t)counts[0] * parts;
+    for (int64_t b = blockIdx.x; b < n; b += gridDim.x) {
+        const int u = (int)(b / parts), part = (int)(b - (int64_t)u * parts);
         const int r = ui(units[u].x), t = ui(units[u].y);
-        wide_tile<DT, R, WideLimits<R>::kThreads>(reqs[r].vol, reqs[r].s, t, L);
+        wide_tile<DT, R, WideLimits<R>::kThreads>(reqs[r].vol, reqs[r].s, t, part, parts, L);
         __syncthreads();
     }
 }
@@ -552,9 +569,10 @@ int64_t staged_tiles(int W, int H) { return (int64_t)((W + kTile - 1) / kTile) *
     }
 
 template <int DT>
-static hipError_t launch_one(const VolDev* vd, int radius, const SliceArgs& s, hipStream_t stream) {
-    const dim3 grid((unsigned)staged_tiles(s.W, s.H));
-#define S(R) hipLaunchKernelGGL((k_reslice_rs<DT, R>), grid, dim3(WideLimits<R>::kThreads), 0, stream, vd, s)
+static hipError_t launch_one(const VolDev* vd, int radius, const SliceArgs& s, int parts, hipStream_t stream) {
+    const dim3 grid((unsigned)(staged_tiles(s.W, s.H) * parts));
+#define S(R) hipLaunchKernelGGL((k_reslice_rs<DT, R>), grid, dim3(WideLimits<R>::kThreads), 0, stream, vd, s, \
+                                parts)
     DARE_DISPATCH_R(radius, S)
 #undef S
     return hipGetLastError();
@@ -571,8 +589,22 @@ static hipError_t launch_many(int radius, const BatchReq* reqs, const int2* unit
     return hipGetLastError();
 }
 
-hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, hipStream_t stream) {
-#define L(D) return launch_one<D>(vd, radius, s, stream)
+// Workgroups per 16 x 16 tile.  Where the output is too coarse for a tile to stage in one piece (its
+// extent beyond about 10 voxels), its pieces are spread over workgroups, up to 64 workgroups per CU
+// in all: few tiles of a coarse view meet the grid, and those hold most of its work.  512 x 512
+// pixels 16 voxels apart at R = 2, 6, 8: 287, 467, 727 us per slice with 8 workgroups per CU, 87, 163,
+// 245 us with 64.
+int staged_parts(int64_t tiles, double pitch_vox) {
+    int edge = kTile;
+    while (edge > 1 && (double)(edge - 1) * pitch_vox > 10.0) edge >>= 1;
+    const int64_t pieces = (int64_t)(kTile / edge) * (kTile / edge);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(pieces, 16384 / std::max<int64_t>(tiles, 1)));
+}
+
+hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, double pitch_vox,
+                                 hipStream_t stream) {
+    const int parts = staged_parts(staged_tiles(s.W, s.H), pitch_vox);
+#define L(D) return launch_one<D>(vd, radius, s, parts, stream)
     DARE_DISPATCH_DT(dtype, L)
 #undef L
 }
