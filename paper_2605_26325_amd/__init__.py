@@ -411,9 +411,9 @@ class Volume:
         import torch
         K = self.info().bins
         nx, ny, nz = self.dims
-        shape = (K, nz, ny, nx)
-        return K, torch.zeros(shape, dtype=dtype, device=self.arena.device), \
-            torch.zeros(shape, dtype=dtype, device=self.arena.device)
+        shape = (K, nz, ny, nx)               # the downloads write every element
+        return K, torch.empty(shape, dtype=dtype, device=self.arena.device), \
+            torch.empty(shape, dtype=dtype, device=self.arena.device)
 
     def download_sums(self, stream=None):
         import torch

@@ -82,24 +82,77 @@ __device__ __forceinline__ int64_t brick_entry(const VolDev* vd, int b, int vx, 
     return (int64_t)b * vd->nbricks + ((int64_t)(vz >> 3) * vd->nby + (vy >> 3)) * vd->nbx + (vx >> 3);
 }
 
-// Pixel block and frame of this workgroup in a flat grid of nbx blocks per frame.  Workgroups
-// are dealt to the 8 XCDs round-robin; when nbx is a multiple of 8, XCD x takes the x-th eighth
-// of every frame's pixel blocks (a band of image rows).  Frames of a sweep are near-parallel, so
-// a band of rows falls on the same part of the volume frame after frame, and each XCD's L2 keeps
-// the accumulators of its own part instead of all eight sharing every line.
-// The launch covers frames f0, f0 + 1, ...
-__device__ __forceinline__ void frame_block(int nbx, int f0, int& bx, int& f) {
-    const int g = blockIdx.x;
-    if ((nbx & 7) == 0) {
-        const int per = nbx >> 3, k = g >> 3;
+// The per-pixel passes take 32 x 32 pixel patches, one per workgroup, four pixels per thread.  A
+// wave's 64 lanes are an 8 x 8 block of the image at a time (four such blocks side by side), not
+// 64 pixels of a row: the block falls on 8 x 8 neighbouring voxels of a brick or four, whose
+// accumulators lie in whole 64-byte cubes of 2 x 2 x 2, where a row of 64 touches 32 cubes in 9
+// bricks.
+constexpr int kPatch = 32;
+
+// Patch (first column and row) and frame of this workgroup in a flat grid of nx x ny patches per
+// frame.  Workgroups are dealt to the 8 XCDs round-robin; when a frame's patches are a multiple of
+// 8, XCD x takes the x-th eighth of every frame's patches (a band of image rows).  Frames of a
+// sweep are near-parallel, so a band of rows falls on the same part of the volume frame after
+// frame, and each XCD's L2 keeps the accumulators of its own part instead of all eight sharing
+// every line.  The launch covers frames f0, f0 + 1, ...
+struct Patch {
+    int i, j, f;
+};
+__device__ __forceinline__ Patch frame_patch(int nx, int ny, int f0) {
+    const int g = blockIdx.x, np = nx * ny;
+    int f, p;
+    if ((np & 7) == 0) {
+        const int per = np >> 3, k = g >> 3;
         f = k / per;
-        bx = (g & 7) * per + (k - f * per);
+        p = (g & 7) * per + (k - f * per);
     } else {
-        f = g / nbx;
-        bx = g - f * nbx;
+        f = g / np;
+        p = g - f * np;
     }
-    f += f0;
+    const int y = p / nx;
+    return Patch{(p - y * nx) * kPatch, y * kPatch, f0 + f};
 }
+
+// Pixel b (0..3) of this thread in its patch.
+__device__ __forceinline__ void patch_pixel(const Patch& p, int b, int& i, int& j) {
+    const int lane = threadIdx.x & 63;
+    i = p.i + b * 8 + (lane & 7);
+    j = p.j + (int)(threadIdx.x >> 6) * 8 + (lane >> 3);
+}
+
+// The (bin, brick) entry and the place in the brick of the four pixels of this thread: entry -1
+// where the pixel lies outside the image or the grid.  Linear-array frames have one bin; a fan
+// frame's columns take the bin of their sector's descriptor.
+template <bool FAN>
+struct FramePixels {
+    PixelView v;
+    FrameDesc fd;
+    int bin;
+    const FanArgs* fan;
+    int first, w;          // fan: the frame's first descriptor, columns
+
+    __device__ __forceinline__ FramePixels(const VolDev* vd, const FanArgs* fan_, int f, int w_) : fan(fan_), w(w_) {
+        v = pixel_view(vd);
+        first = FAN ? f * fan->sectors : f;
+        fd = frame_uniform(v, first);   // a frame's descriptors share its placement
+        bin = *((cptr<int32_t>)v.frame_bin + first);
+    }
+    __device__ __forceinline__ int64_t entry(int i, int j, int h, double sx, double sy, int& local) const {
+        int vx = 0, vy = 0, vz = 0;
+        local = 0;
+        if (i >= w || j >= h) return -1;
+        int b = bin;
+        bool ok;
+        if constexpr (FAN) {
+            ok = fan_voxel(&fd, v.origin, v.inv_h, v.nx, v.ny, v.nz, *fan, i, j, vx, vy, vz);
+            b = ((gptr<const int32_t>)v.frame_bin)[first + i * fan->sectors / w];
+        } else {
+            ok = frame_voxel(&fd, v.origin, v.inv_h, v.nx, v.ny, v.nz, i, j, sx, sy, vx, vy, vz);
+        }
+        local = brick_local(vx, vy, vz);
+        return ok ? brick_entry(v, b, vx, vy, vz) : -1;
+    }
+};
 
 }  // namespace
 
@@ -114,13 +167,17 @@ __global__ void k_compose_frames(VolDev* vd, const float* __restrict__ poses, in
 
 // K2: leader clustering of frame orientations, frames in order, by one workgroup.  The
 // sequential rule (an entry joins its best qualifying bin, else opens a new one, else, with the
-// codebook full, joins its best bin overall) only changes the codebook when an entry opens a bin,
-// so chunks of 256 consecutive entries are tested in parallel against the current codebook:
-// every entry before the chunk's first opener is final as tested, the opener takes the next bin,
-// and the scan resumes after it.  Identical results in at most n / 256 + max_bins steps.
-__global__ void __launch_bounds__(256) k_assign_bins(VolDev* vd, int n, int K0) {
+// codebook full, joins its best bin overall) only changes the codebook when an entry opens a bin.
+// So chunks of consecutive entries are tested in parallel against the current codebook, one entry
+// per thread, which keeps its best bins so far; every entry before the chunk's first opener is
+// final, the opener takes the next bin, and the entries after it test that one bin more.  Identical
+// results in n / 512 passes over the codebook and at most max_bins tests of one bin.  Bound: the
+// chain of FP64 dot products and barriers of one workgroup; 2400 (frame, sector) entries that open
+// 64 bins take 98 us, against 283 with the whole codebook tested again after every opener.
+constexpr int kAssign = 512;
+__global__ void __launch_bounds__(kAssign) k_assign_bins(VolDev* vd, int n, int K0) {
     __shared__ double rep[kMaxBins][6];   // per bin: representative normal, then in-plane axis
-    __shared__ int s_first, s_sat;
+    __shared__ int s_first[2], s_sat;     // the chunk's next opener: one in use, one being reset
     const int tid = threadIdx.x;
     if (tid < K0) {
 #pragma unroll
@@ -130,17 +187,18 @@ __global__ void __launch_bounds__(256) k_assign_bins(VolDev* vd, int n, int K0) 
         }
     }
     if (tid == 0) {
-        s_first = 256;
+        s_first[0] = s_first[1] = kAssign;
         s_sat = vd->st.saturated;
     }
-    int K = K0;
+    int K = K0, turn = 0;
     const double ct = vd->cos_tol;
     const int kmax = vd->max_bins;
-    for (int base = 0; base < n;) {
-        __syncthreads();
+    __syncthreads();
+    for (int base = 0; base < n; base += kAssign) {
         const int f = base + tid;
         double nf[3] = {0, 0, 0}, xf[3] = {0, 0, 0};
         int best = -1, any = -1;
+        double best_s = -INFINITY, any_s = -INFINITY;
         if (f < n) {
             const FrameDesc* fd = vd->frames + f;
 #pragma unroll
@@ -148,45 +206,47 @@ __global__ void __launch_bounds__(256) k_assign_bins(VolDev* vd, int n, int K0) 
                 nf[a] = fd->nh[a];
                 xf[a] = fd->xh[a];
             }
-            double best_s = -INFINITY, any_s = -INFINITY;
-            for (int b = 0; b < K; ++b) {   // strict > keeps the lowest index on ties
-                const double rn[3] = {rep[b][0], rep[b][1], rep[b][2]};
-                const double rx[3] = {rep[b][3], rep[b][4], rep[b][5]};
-                const double dn = dot3(nf, rn);
-                const double di = fabs(dot3(xf, rx));
-                const double sc = dn + di;
-                if (sc > any_s) {
-                    any_s = sc;
-                    any = b;
-                }
-                if (dn >= ct && di >= ct && sc > best_s) {
-                    best_s = sc;
-                    best = b;
+        }
+        auto test = [&](int b) {   // strict > keeps the lowest index on ties
+            const double rn[3] = {rep[b][0], rep[b][1], rep[b][2]};
+            const double rx[3] = {rep[b][3], rep[b][4], rep[b][5]};
+            const double dn = dot3(nf, rn);
+            const double di = fabs(dot3(xf, rx));
+            const double sc = dn + di;
+            if (sc > any_s) {
+                any_s = sc;
+                any = b;
+            }
+            if (dn >= ct && di >= ct && sc > best_s) {
+                best_s = sc;
+                best = b;
+            }
+        };
+        for (int b = 0; b < K; ++b) test(b);
+        for (int done = 0;; ) {    // entries before `done` are final
+            if (f < n && tid >= done && best < 0 && K < kmax) atomicMin(&s_first[turn], tid);
+            __syncthreads();
+            const int p = s_first[turn];
+            turn ^= 1;
+            if (tid == 0) s_first[turn] = kAssign;
+            if (p == kAssign) break;
+            if (tid == p) {
+                best = K;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    rep[K][a] = nf[a];
+                    rep[K][3 + a] = xf[a];
                 }
             }
-            if (best < 0 && K < kmax) atomicMin(&s_first, tid);
+            __syncthreads();
+            if (tid > p) test(K);
+            ++K;
+            done = p + 1;
         }
         __syncthreads();
-        const int p = s_first;
-        if (f < n && tid < p) {
+        if (f < n) {
             vd->frame_bin[f] = best >= 0 ? best : any;
             if (best < 0) s_sat = 1;   // only with the codebook full
-        }
-        if (tid == p) {
-            vd->frame_bin[f] = K;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                rep[K][a] = nf[a];
-                rep[K][3 + a] = xf[a];
-            }
-        }
-        __syncthreads();
-        if (tid == 0) s_first = 256;
-        if (p < 256) {
-            ++K;
-            base += p + 1;
-        } else {
-            base += 256;
         }
     }
     __syncthreads();
@@ -203,47 +263,100 @@ __global__ void __launch_bounds__(256) k_assign_bins(VolDev* vd, int n, int K0) 
     }
 }
 
-__device__ __forceinline__ void mark_entry(VolDev* vd, int64_t e) {
+// Marks entry e; returns what this call was first to do: kNew, the entry's mark (-1 -> -2), or
+// kDirty, the flag of a resident brick (its slot in `slot`).  The caller appends either to its
+// list.  The first reads are at agent scope: through the caches an XCD would keep its stale copy
+// and go on to the atomic every time.
+enum Marked { kSeen, kNew, kDirty };
+__device__ __forceinline__ Marked mark_entry(VolDev* vd, int64_t e, int& slot) {
     const gptr<int32_t> te = (gptr<int32_t>)vd->table + e;
     const int cur = __hip_atomic_load(te, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    slot = cur;
     if (cur == -1) {
         int expected = -1;
-        if (__hip_atomic_compare_exchange_strong(te, &expected, -2, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT)) {
-            const uint32_t k = atomicAdd(&vd->st.new_count, 1u);
-            if (k < vd->cap) ((gptr<int32_t>)vd->new_list)[k] = (int32_t)e;
-        }
-    } else if (cur >= 0) {
-        const gptr<uint32_t> fl = (gptr<uint32_t>)vd->dirty_flags + cur;
-        if (__hip_atomic_load(fl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
-            __hip_atomic_exchange(fl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
-            const uint32_t d = atomicAdd(&vd->st.dirty_count, 1u);
-            ((gptr<int32_t>)vd->dirty_list)[d] = cur;
+        return __hip_atomic_compare_exchange_strong(te, &expected, -2, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT) ? kNew : kSeen;
+    }
+    if (cur < 0) return kSeen;
+    const gptr<uint32_t> fl = (gptr<uint32_t>)vd->dirty_flags + cur;
+    return __hip_atomic_load(fl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
+                   __hip_atomic_exchange(fl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u ? kDirty : kSeen;
+}
+
+// The k-th new entry or dirty slot of the batch into its list.
+__device__ __forceinline__ void append_new(VolDev* vd, uint32_t k, int64_t e) {
+    if (k < vd->cap) ((gptr<int32_t>)vd->new_list)[k] = (int32_t)e;
+}
+__device__ __forceinline__ void append_dirty(VolDev* vd, uint32_t k, int slot) {
+    ((gptr<int32_t>)vd->dirty_list)[k] = slot;
+}
+__device__ __forceinline__ void mark_one(VolDev* vd, int64_t e) {
+    int slot;
+    const Marked m = mark_entry(vd, e, slot);
+    if (m == kNew) append_new(vd, atomicAdd(&vd->st.new_count, 1u), e);
+    if (m == kDirty) append_dirty(vd, atomicAdd(&vd->st.dirty_count, 1u), slot);
+}
+
+// K3a: mark every (bin, brick) that a pixel of the batch lands in.  A lane whose left or upper
+// neighbour in the wave's block holds the same entry leaves it to that lane; what remains goes
+// into a set of the workgroup's entries in LDS (about 40 for 1024 pixels), which its threads then
+// mark side by side, and a workgroup takes its places in the two lists with one addition each.
+// What bounds the pass is what crosses the XCDs: additions to the lists' counters above all (a
+// counter takes one about every 5 ns; one per wave made 1490 us of 1800 frames of 256^2, one per
+// workgroup 480), then the chain of a mark's read, exchange and store, gone through once per 1024
+// pixels (2730 us when the four blocks marked in turn).  One mark per run of a 64-pixel row, each
+// with its own addition, took 1190 us; 30 frames of 512^2 into resident bricks 254 -> 71 us.
+constexpr int kMarkSet = 256;
+template <bool FAN>
+__device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, double sx, double sy, const FanArgs* fan, int f0) {
+    __shared__ int set[kMarkSet];
+    __shared__ uint32_t count[2], first[2];   // the workgroup's new entries and dirty slots
+    if (threadIdx.x < 2) count[threadIdx.x] = 0u;
+    for (int k = threadIdx.x; k < kMarkSet; k += 256) set[k] = -1;
+    const Patch p = frame_patch((w + kPatch - 1) / kPatch, (h + kPatch - 1) / kPatch, f0);
+    const FramePixels<FAN> px(vd, fan, p.f, w);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        int i, j, local;
+        patch_pixel(p, b, i, j);
+        const int e = (int)px.entry(i, j, h, sx, sy, local);   // entries fit the lists' 32 bits
+        const int left = __shfl_up(e, 1), up = __shfl_up(e, 8);
+        bool mine = e >= 0 && !(lane >= 1 && left == e) && !(lane >= 8 && up == e);
+        if (mine) {
+            uint32_t at = ((uint32_t)e * 2654435761u) >> 24;
+            for (int probe = 0; probe < 8; ++probe, at = (at + 1) & (kMarkSet - 1)) {
+                const int was = atomicCAS(&set[at], -1, e);
+                mine = was != -1 && was != e;
+                if (!mine) break;
+            }
+            if (mine) mark_one(vd, e);   // no free place for it
         }
     }
+    __syncthreads();
+    const int e = set[threadIdx.x];
+    int slot = -1;
+    const Marked m = e >= 0 ? mark_entry(vd, e, slot) : kSeen;
+    // places in the lists: one addition to each counter per workgroup that has any
+    const unsigned long long nm = __ballot(m == kNew), dm = __ballot(m == kDirty);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t base_n = 0, base_d = 0;
+    if (lane == 0 && nm) base_n = atomicAdd(&count[0], (uint32_t)__popcll(nm));
+    if (lane == 0 && dm) base_d = atomicAdd(&count[1], (uint32_t)__popcll(dm));
+    // lane 0's values, taken while the whole wave is active
+    const uint32_t at_n = __builtin_amdgcn_readfirstlane(base_n) + __popcll(nm & below);
+    const uint32_t at_d = __builtin_amdgcn_readfirstlane(base_d) + __popcll(dm & below);
+    __syncthreads();
+    if (threadIdx.x < 2 && count[threadIdx.x])
+        first[threadIdx.x] = atomicAdd(threadIdx.x ? &vd->st.dirty_count : &vd->st.new_count, count[threadIdx.x]);
+    __syncthreads();
+    if (m == kNew) append_new(vd, first[0] + at_n, e);
+    if (m == kDirty) append_dirty(vd, first[1] + at_d, slot);
 }
 
-// Marks the entry of each lane that has one, except where the lane before it in the wave holds
-// the same entry (neighbouring pixels mostly land in one brick): that lane marks it, which is
-// all a mark needs.  Every lane of the wave must call this.
-__device__ __forceinline__ void mark_wave(VolDev* vd, int64_t e) {
-    const int64_t prev = __shfl_up(e, 1);
-    if (e >= 0 && ((threadIdx.x & 63) == 0 || prev != e)) mark_entry(vd, e);
-}
-
-// K3a: mark every (bin, brick) that a pixel of the batch lands in.
 __global__ void __launch_bounds__(256) k_mark_pixels(VolDev* vd, int w, int h, double sx, double sy, int f0) {
-    int bx, f;
-    frame_block((w * h + 255) >> 8, f0, bx, f);
-    const PixelView v = pixel_view(vd);
-    const FrameDesc fd = frame_uniform(v, f);
-    const int bin = *((cptr<int32_t>)v.frame_bin + f);
-    const int pix = bx * 256 + threadIdx.x;
-    int64_t e = -1;
-    int vx, vy, vz;
-    if (pix < w * h && frame_voxel(&fd, v.origin, v.inv_h, v.nx, v.ny, v.nz, pix % w, pix / w, sx, sy, vx, vy, vz))
-        e = brick_entry(v, bin, vx, vy, vz);
-    mark_wave(vd, e);
+    mark_patch<false>(vd, w, h, sx, sy, nullptr, f0);
 }
 
 // Fan probes: one frame descriptor per (frame, sector), each with the frame's pose and the
@@ -258,20 +371,9 @@ __global__ void k_compose_fan(VolDev* vd, const float* __restrict__ poses, int n
     vd->frames[k] = d;
 }
 
-// K3a for fan frames: the pixel's (frame, sector) descriptor gives its pose and bin.
+// K3a for fan frames.
 __global__ void __launch_bounds__(256) k_mark_fan(VolDev* vd, int w, int h, FanArgs fan, int f0) {
-    int bx, f;
-    frame_block((w * h + 255) >> 8, f0, bx, f);
-    const int pix = bx * 256 + threadIdx.x;
-    int64_t entry = -1;
-    if (pix < w * h) {
-        const int i = pix % w, j = pix / w;
-        const int e = f * fan.sectors + i * fan.sectors / w;
-        int vx, vy, vz;
-        if (fan_voxel(vd->frames + e, vd->origin, vd->inv_h, vd->nx, vd->ny, vd->nz, fan, i, j, vx, vy, vz))
-            entry = brick_entry(vd, vd->frame_bin[e], vx, vy, vz);
-    }
-    mark_wave(vd, entry);
+    mark_patch<true>(vd, w, h, 0.0, 0.0, &fan, f0);
 }
 
 // Undo the marks of a rejected batch and restore the codebook size.
@@ -309,45 +411,87 @@ __global__ void __launch_bounds__(256) k_alloc(VolDev* vd, uint32_t new_count, u
     }
 }
 
-// K4: add each pixel's intensity and a count to its (bin, voxel).
+// Pixels of one voxel among a wave's 8 x 8 block are added up before they go to memory: halving
+// steps along the rows, then across them, each lane taking over its partner's sum where both hold
+// the same (slot, voxel); `place` of a lane taken over becomes -1.  Steps are skipped once no
+// lane has such a partner (frames at a voxel per pixel: one comparison).
+template <int D>
+__device__ __forceinline__ int lane_plus(int x) {   // lane + D's value, D within a row of 16 lanes
+    return __builtin_amdgcn_update_dpp(0, x, 0x100 + D, 0xF, 0xF, true);
+}
+template <int D>
+__device__ __forceinline__ bool merge_step(int lane, int& place, int local, uint32_t& add) {
+    int op, ol;
+    uint32_t oa;
+    if constexpr (D < 16) {
+        op = lane_plus<D>(place);
+        ol = lane_plus<D>(local);
+        oa = (uint32_t)lane_plus<D>((int)add);
+    } else {
+        op = __shfl_down(place, D);
+        ol = __shfl_down(local, D);
+        oa = (uint32_t)__shfl_down((int)add, D);
+    }
+    const bool take = (lane & (2 * D - 1)) < D && (D >= 8 || (lane & (D - 1)) == 0) && place >= 0 && op == place && ol == local;
+    const unsigned long long m = __ballot(take);
+    if (take) add += oa;
+    if ((m >> ((lane - D) & 63)) & 1ull && lane >= D) place = -1;
+    return m != 0;
+}
+__device__ __forceinline__ void merge_pixels(int& place, int local, uint32_t& add) {
+    const int lane = threadIdx.x & 63;
+    if (merge_step<1>(lane, place, local, add) && merge_step<2>(lane, place, local, add)) merge_step<4>(lane, place, local, add);
+    if (merge_step<8>(lane, place, local, add) && merge_step<16>(lane, place, local, add)) merge_step<32>(lane, place, local, add);
+}
+
+// K4: add each pixel's intensity and a count to its (bin, voxel).  Bound by the rate at which
+// memory takes the atomic requests (they go past the L2s, which do not share lines between XCDs):
+// 40 M requests of up to 64 bytes for the 100 M in-grid pixels of 1800 frames of 256^2, 1660 us.  With
+// the wave's 64 pixels along a row instead of an 8 x 8 block it was 2730 us.  Merging pixels of one
+// voxel first takes 300 fan frames (about 6 pixels a voxel) from 523 to 188 us.
+template <bool FAN>
+__device__ __forceinline__ void accumulate_patch(const VolDev* __restrict__ vd, const uint8_t* __restrict__ frames,
+                                                 int w, int h, double sx, double sy, const FanArgs* fan, int f0) {
+    const Patch p = frame_patch((w + kPatch - 1) / kPatch, (h + kPatch - 1) / kPatch, f0);
+    const FramePixels<FAN> px(vd, fan, p.f, w);
+    const gptr<unsigned long long> acc = (gptr<unsigned long long>)((cptr<VolDev>)vd)->acc;
+    const gptr<const uint8_t> img = (gptr<const uint8_t>)frames + (size_t)p.f * w * h;
+    // the four pixels and their table entries, all loads in flight together (a lane without a
+    // voxel reads entry 0 of each, and drops what it reads)
+    int64_t e[4];
+    int local[4], slot[4];
+    uint32_t inten[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        int i, j;
+        patch_pixel(p, b, i, j);
+        e[b] = px.entry(i, j, h, sx, sy, local[b]);
+        inten[b] = img[e[b] >= 0 ? (size_t)j * w + i : 0];
+        slot[b] = ((gptr<const int32_t>)px.v.table)[e[b] >= 0 ? e[b] : 0];
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        // slot < 0 is unreachable: every entry hit was marked and allocated
+        int place = e[b] >= 0 ? slot[b] : -1;
+        uint32_t add = inten[b] << 8 | 1u;   // sum and count of up to 64 pixels
+        merge_pixels(place, local[b], add);
+        if (place >= 0)
+            __hip_atomic_fetch_add(acc + (size_t)place * kBrickVox + local[b],
+                                   ((unsigned long long)(add >> 8) << 32) | (add & 255u), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 __global__ void __launch_bounds__(256) k_accumulate(const VolDev* __restrict__ vd, const uint8_t* __restrict__ frames,
                                                     int w, int h, double sx, double sy, int f0) {
-    int bx, f;
-    frame_block((w * h + 255) >> 8, f0, bx, f);
-    const PixelView v = pixel_view(vd);
-    const FrameDesc fd = frame_uniform(v, f);
-    const int bin = *((cptr<int32_t>)v.frame_bin + f);
-    const gptr<unsigned long long> acc = (gptr<unsigned long long>)((cptr<VolDev>)vd)->acc;
-    const int pix = bx * 256 + threadIdx.x;
-    int vx = 0, vy = 0, vz = 0;
-    const bool ok =
-        pix < w * h && frame_voxel(&fd, v.origin, v.inv_h, v.nx, v.ny, v.nz, pix % w, pix / w, sx, sy, vx, vy, vz);
-    // the pixel and its table entry, both loads in flight together (lanes without a voxel read
-    // entry 0 of each, and drop what they read)
-    const unsigned long long inten = ((gptr<const uint8_t>)frames)[ok ? (size_t)f * w * h + pix : 0];
-    const int slot = ((gptr<const int32_t>)v.table)[ok ? brick_entry(v, bin, vx, vy, vz) : 0];
-    asm volatile("" ::"v"(inten), "v"(slot));
-    if (!ok || slot < 0) return;   // slot < 0 is unreachable: every entry hit was marked and allocated
-    __hip_atomic_fetch_add(acc + (size_t)slot * kBrickVox + brick_local(vx, vy, vz), (inten << 32) | 1ull,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    accumulate_patch<false>(vd, frames, w, h, sx, sy, nullptr, f0);
 }
 
 // K4 for fan frames.
 __global__ void __launch_bounds__(256) k_accumulate_fan(const VolDev* __restrict__ vd,
                                                         const uint8_t* __restrict__ frames, int w, int h, FanArgs fan,
                                                         int f0) {
-    int bx, f;
-    frame_block((w * h + 255) >> 8, f0, bx, f);
-    const int pix = bx * 256 + threadIdx.x;
-    if (pix >= w * h) return;
-    const int i = pix % w, j = pix / w;
-    const int e = f * fan.sectors + i * fan.sectors / w;
-    int vx, vy, vz;
-    if (!fan_voxel(vd->frames + e, vd->origin, vd->inv_h, vd->nx, vd->ny, vd->nz, fan, i, j, vx, vy, vz)) return;
-    const int slot = vd->table[brick_entry(vd, vd->frame_bin[e], vx, vy, vz)];
-    if (slot < 0) return;   // unreachable: every entry hit here was marked and allocated
-    const unsigned long long inten = frames[(size_t)f * w * h + pix];
-    atomicAdd(vd->acc + (size_t)slot * kBrickVox + brick_local(vx, vy, vz), (inten << 32) | 1ull);
+    accumulate_patch<true>(vd, frames, w, h, 0.0, 0.0, &fan, f0);
 }
 
 // K5: exact sums -> stored (value, count) pairs of every dirty slot.
@@ -453,7 +597,7 @@ __global__ void k_dense_mark(VolDev* vd, const uint32_t* __restrict__ C, int K) 
         r /= vd->nx;
         const int vy = (int)(r % vd->ny);
         const int vz = (int)(r / vd->ny);
-        mark_entry(vd, brick_entry(vd, b, vx, vy, vz));
+        mark_one(vd, brick_entry(vd, b, vx, vy, vz));
     }
 }
 
@@ -475,21 +619,43 @@ __global__ void k_dense_scatter(const VolDev* vd, const uint32_t* __restrict__ S
     }
 }
 
-__global__ void k_download_sums(const VolDev* vd, uint32_t* __restrict__ S, uint32_t* __restrict__ C, int K) {
-    const int64_t nvox = (int64_t)vd->nx * vd->ny * vd->nz;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nvox * K;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int b = (int)(k / nvox);
-        int64_t r = k - b * nvox;
-        const int vx = (int)(r % vd->nx);
-        r /= vd->nx;
-        const int vy = (int)(r % vd->ny);
-        const int vz = (int)(r / vd->ny);
-        const int slot = vd->table[brick_entry(vd, b, vx, vy, vz)];
-        unsigned long long u = 0ull;
-        if (slot >= 0) u = vd->acc[(size_t)slot * kBrickVox + brick_local(vx, vy, vz)];
-        S[k] = (uint32_t)(u >> 32);
-        C[k] = (uint32_t)(u & 0xFFFFFFFFull);
+// Every voxel's exact sum and count as dense arrays.  A wave takes a row of 8 bricks along x (64
+// voxels) and stores it row by row, so that the waves of a workgroup, at consecutive rows of bricks,
+// fill long runs in order; its loads go cube by cube, so each line of a brick is read once.  Bound by
+// the bytes (3.5 GB written and 2 GB read for 26 bins of 256^3): 1150 us, 4.8 TB/s; a thread per
+// voxel index, with its 64-bit divisions, took 2610 us, and rows of 8 bricks stored 64 rows apart
+// (8 waves' worth of scattered 256-byte pieces) 3930 us.
+__global__ void __launch_bounds__(256) k_download_sums(const VolDev* __restrict__ vd, uint32_t* __restrict__ S,
+                                                       uint32_t* __restrict__ C, int b0, int64_t items) {
+    int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // (bin, bz, by, row of bricks)
+    if (g >= items) return;
+    const int nxr = (vd->nbx + 7) / 8, nx = vd->nx, ny = vd->ny, nz = vd->nz;
+    const int lane = threadIdx.x & 63;
+    const int vx = (int)(g % nxr) * 64 + lane;
+    g /= nxr;
+    const int y0 = (int)(g % vd->nby) * 8;
+    g /= vd->nby;
+    const int z0 = (int)(g % vd->nbz) * 8, bin = (int)(g / vd->nbz);
+    const bool in = vx < nx;
+    const int slot = in ? vd->table[brick_entry(vd, b0 + bin, vx, y0, z0)] : -1;
+    const gptr<const unsigned long long> acc = (gptr<const unsigned long long>)vd->acc + (size_t)max(slot, 0) * kBrickVox;
+    for (int z = 0; z < 8; z += 2) {
+        unsigned long long u[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            u[k] = 0ull;
+            if (slot >= 0) u[k] = acc[brick_local(vx, k >> 1, z + (k & 1))];
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int vz = z0 + z + (k >> 3), vy = y0 + (k & 7);
+            const unsigned long long x = u[((k & 7) << 1) | (k >> 3)];
+            if (!in || vy >= ny || vz >= nz) continue;
+            const size_t at = (((size_t)bin * nz + vz) * ny + vy) * nx + vx;
+            // written once, read by no kernel here: past the caches
+            __builtin_nontemporal_store((uint32_t)(x >> 32), S + at);
+            __builtin_nontemporal_store((uint32_t)(x & 0xFFFFFFFFull), C + at);
+        }
     }
 }
 
@@ -531,11 +697,14 @@ static inline int grid_for(int64_t n, int block, int cap = 65536) {
     return (int)(g > cap ? cap : g);
 }
 
-// Frames per launch of the per-pixel passes (flat grids of pixel blocks x frames), so that a
-// grid stays below 2^24 workgroups.
+static int64_t frame_patches(int w, int h) {
+    return (int64_t)((w + kPatch - 1) / kPatch) * ((h + kPatch - 1) / kPatch);
+}
+
+// Frames per launch of the per-pixel passes (flat grids of patches x frames), so that a grid stays
+// below 2^24 workgroups.
 int frames_per_launch(int n, int w, int h) {
-    const int64_t nbx = ((int64_t)w * h + 255) / 256;
-    const int64_t fc = ((int64_t)1 << 24) / nbx;
+    const int64_t fc = ((int64_t)1 << 24) / frame_patches(w, h);
     return (int)std::max<int64_t>(1, std::min<int64_t>(n, fc));
 }
 
@@ -545,14 +714,14 @@ hipError_t launch_compose_frames(const VolDev* vd, const float* poses, int n, hi
 }
 
 hipError_t launch_assign_bins(VolDev* vd, int n, int K0, hipStream_t stream) {
-    hipLaunchKernelGGL(k_assign_bins, dim3(1), dim3(256), 0, stream, vd, n, K0);
+    hipLaunchKernelGGL(k_assign_bins, dim3(1), dim3(kAssign), 0, stream, vd, n, K0);
     return hipGetLastError();
 }
 
 hipError_t launch_mark_pixels(const VolDev* vd, int n, int w, int h, double sx, double sy, hipStream_t stream) {
-    const int nbx = (w * h + 255) / 256, fc = frames_per_launch(n, w, h);
+    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
     for (int f0 = 0; f0 < n; f0 += fc)
-        hipLaunchKernelGGL(k_mark_pixels, dim3(nbx * std::min(fc, n - f0)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(k_mark_pixels, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream,
                            const_cast<VolDev*>(vd), w, h, sx, sy, f0);
     return hipGetLastError();
 }
@@ -566,18 +735,18 @@ hipError_t launch_compose_fan(const VolDev* vd, const float* poses, int n, const
 }
 
 hipError_t launch_mark_fan(const VolDev* vd, int n, int w, int h, const FanArgs& fan, hipStream_t stream) {
-    const int nbx = (w * h + 255) / 256, fc = frames_per_launch(n, w, h);
+    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
     for (int f0 = 0; f0 < n; f0 += fc)
-        hipLaunchKernelGGL(k_mark_fan, dim3(nbx * std::min(fc, n - f0)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(k_mark_fan, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream,
                            const_cast<VolDev*>(vd), w, h, fan, f0);
     return hipGetLastError();
 }
 
 hipError_t launch_accumulate_fan(const VolDev* vd, const uint8_t* frames, int n, int w, int h, const FanArgs& fan,
                                  hipStream_t stream) {
-    const int nbx = (w * h + 255) / 256, fc = frames_per_launch(n, w, h);
+    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
     for (int f0 = 0; f0 < n; f0 += fc)
-        hipLaunchKernelGGL(k_accumulate_fan, dim3(nbx * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h,
+        hipLaunchKernelGGL(k_accumulate_fan, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h,
                            fan, f0);
     return hipGetLastError();
 }
@@ -598,9 +767,9 @@ hipError_t launch_alloc(VolDev* vd, uint32_t new_count, uint32_t used, uint32_t 
 
 hipError_t launch_accumulate(const VolDev* vd, const uint8_t* frames, int n, int w, int h, double sx, double sy,
                              hipStream_t stream) {
-    const int nbx = (w * h + 255) / 256, fc = frames_per_launch(n, w, h);
+    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
     for (int f0 = 0; f0 < n; f0 += fc)
-        hipLaunchKernelGGL(k_accumulate, dim3(nbx * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h, sx,
+        hipLaunchKernelGGL(k_accumulate, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h, sx,
                            sy, f0);
     return hipGetLastError();
 }
@@ -639,9 +808,14 @@ hipError_t launch_dense_scatter(const VolDev* vd, const uint32_t* S, const uint3
     return hipGetLastError();
 }
 
-hipError_t launch_download_sums(const VolDev* vd, uint32_t* S, uint32_t* C, int K, int, int, int,
+hipError_t launch_download_sums(const VolDev* vd, uint32_t* S, uint32_t* C, int K, int nx, int ny, int nz,
                                 hipStream_t stream) {
-    hipLaunchKernelGGL(k_download_sums, dim3(4096), dim3(256), 0, stream, vd, S, C, K);
+    const int64_t rows = (int64_t)((nx + 63) / 64) * ((ny + 7) / 8) * ((nz + 7) / 8);
+    const int per = (int)std::max<int64_t>(1, ((int64_t)1 << 23) / rows);   // bins per launch
+    const size_t nvox = (size_t)nx * ny * nz;
+    for (int b0 = 0; b0 < K; b0 += per)
+        hipLaunchKernelGGL(k_download_sums, dim3((unsigned)((rows * std::min(per, K - b0) + 3) / 4)), dim3(256), 0,
+                           stream, vd, S + b0 * nvox, C + b0 * nvox, b0, rows * std::min(per, K - b0));
     return hipGetLastError();
 }
 
