@@ -118,26 +118,44 @@ __device__ __forceinline__ Plane plane_of(const SliceRec& rec) {
     return pl;
 }
 
-// Does a T x T tile of this request fit the LDS budget wherever it falls?
-__device__ __forceinline__ bool tile_fits(const Plane& pl, int T) {
+// Does the voxel box of a T x T tile of this request fit the LDS budget wherever it falls, but for its
+// table entries: `nbb` bricks at most.
+__device__ __forceinline__ bool box_fits(const Plane& pl, int T, int& nbb) {
     const int dax = pl.f.dax, pax = dax == 0 ? 1 : 0, qax = dax == 2 ? 1 : 2;
     int e[3];
-    int64_t nbb = 1;
+    int64_t nb = 1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         e[a] = box_edge_bound(T, pl.ex[a], pl.ey[a]);
-        nbb *= e[a] / 8 + 2;
+        nb *= e[a] / 8 + 2;
     }
+    nbb = (int)(nb < kSlotsMax ? nb : kSlotsMax);
     const int64_t cols = (int64_t)pick3(e, pax) * pick3(e, qax);
-    const int kactp = (pl.kact + 7) & ~7;
-    return cols <= kColsMax && cols * pl.depth <= kItemsMax && nbb * kactp <= kSlotsMax && pick3(e, dax) <= kRunSpan &&
-           pl.depth <= kRunSpan;
+    return cols <= kColsMax && cols * pl.depth <= kItemsMax && pick3(e, dax) <= kRunSpan && pl.depth <= kRunSpan;
 }
 
-// One lane: the request's plane in voxel coordinates (FP64), its frame, volume view and output,
-// and the slab of a tile: voxels with |m.(v - c0)| < |m|_1 (plus slop for FP32 rounding of
-// coordinates up to the grid's size) form runs of at most ceil(2 half) voxels along dax.  Stored
-// in `rec` and returned (tile edge and surviving bins not yet set).
+// Bins per slot row, and whether the table entries of nbb bricks fit too.
+__device__ __forceinline__ int row_bins(int kact) { return (kact + 7) & ~7; }
+__device__ __forceinline__ bool slots_fit(int nbb, int kact) { return nbb * row_bins(kact) <= kSlotsMax; }
+
+// Does a T x T tile of this request fit the LDS budget wherever it falls?
+__device__ __forceinline__ bool tile_fits(const Plane& pl, int T) {
+    int nbb;
+    return box_fits(pl, T, nbb) && slots_fit(nbb, pl.kact);
+}
+
+// The slab of a tile from the plane's frame: voxels with |m.(v - c0)| < |m|_1 (plus slop for FP32
+// rounding of coordinates up to the grid's size) form runs of at most ceil(2 half) voxels along dax.
+__device__ __forceinline__ void plane_slab(int nx, int ny, int nz, Plane& pl) {
+    const int nmax = max(nx, max(ny, nz));
+    pl.slop = 2e-3f + 1e-6f * (float)(nmax + 64);
+    const float l1m = fabsf(pl.f.fm[0]) + fabsf(pl.f.fm[1]) + fabsf(pl.f.fm[2]);
+    pl.half = (l1m + pl.slop) * fabsf(1.0f / pick3(pl.f.fm, pl.f.dax));
+    pl.depth = (int)ceilf(2.0f * pl.half);
+}
+
+// One lane: the request's plane in voxel coordinates (FP64), its frame, volume view and output, and
+// its slab.  Stored in `rec` and returned (tile edge and surviving bins not yet set).
 __device__ __forceinline__ Plane request_frame(const VolDev* __restrict__ vd, const SliceArgs& s, const double T[12],
                                                SliceRec& rec) {
     Plane pl;
@@ -160,11 +178,7 @@ __device__ __forceinline__ Plane request_frame(const VolDev* __restrict__ vd, co
     rec.H = pl.H = s.H;
 #pragma unroll
     for (int a = 0; a < 3; ++a) pl.n[a] = vv.n[a];
-    const int nmax = max(vv.n[0], max(vv.n[1], vv.n[2]));
-    pl.slop = 2e-3f + 1e-6f * (float)(nmax + 64);
-    const float l1m = fabsf(pl.f.fm[0]) + fabsf(pl.f.fm[1]) + fabsf(pl.f.fm[2]);
-    pl.half = (l1m + pl.slop) * fabsf(1.0f / pick3(pl.f.fm, pl.f.dax));
-    pl.depth = (int)ceilf(2.0f * pl.half);
+    plane_slab(vv.n[0], vv.n[1], vv.n[2], pl);
     rec.slop = pl.slop;
     rec.half = pl.half;
     rec.depth = pl.depth;
@@ -252,55 +266,63 @@ __device__ __forceinline__ void tile_box(const double (&c00)[3], const double (&
     tr.m_bdy = small_div(max(tr.bdim[1], 1)).m;
 }
 
-// One thread, after `tile_box`: the part of the record that needs the plane's frame (the box's
-// columns along the dominant axis, whether they fit the LDS budget, the slab and lateral
-// thresholds), all but what depends on the number of surviving bins (`tile_bins`).
-__device__ __forceinline__ void tile_frame(const Plane& pl, TileRec& tr) {
-    const int dax = pl.f.dax, pax = dax == 0 ? 1 : 0, qax = dax == 2 ? 1 : 2;
-    const int lo[3] = {tr.lo[0], tr.lo[1], tr.lo[2]}, hi[3] = {tr.hi[0], tr.hi[1], tr.hi[2]};
-    const int bp = pick3(hi, pax) - pick3(lo, pax) + 1, bq = pick3(hi, qax) - pick3(lo, qax) + 1;
-    const int depth = pl.depth;
-    // the request's bound makes every staged tile fit; a tile beyond it would be left NaN, so the
-    // check only keeps the LDS accesses in bounds
-    const bool fits = bp >= 2 && bq >= 2 && depth >= 2 && depth <= kRunSpan && bp * bq <= kColsMax &&
-                      bp * bq * depth <= kItemsMax && pick3(hi, dax) - pick3(lo, dax) <= kRunSpan;
-    tr.mode = (tr.mode == 1 && fits) ? 1 : 0;
+// One thread: the slab and lateral thresholds, which need only the plane's frame.  Every voxel with
+// weight for a pixel of the tile lies within |m.(v - c0)| < |m|_1 and, along the in-plane axes,
+// within the tile's extent widened by |u|_1, |w|_1 (the margins cover FP32 rounding and the pose
+// rigidity tolerance).
+__device__ __forceinline__ void tile_slab(const Plane& pl, TileRec& tr) {
     float l1u = 0.0f, l1w = 0.0f;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         l1u += fabsf(pl.f.fu[a]);
         l1w += fabsf(pl.f.fw[a]);
     }
-    tr.bp = bp;
-    tr.bq = bq;
-    tr.ncols = bp * bq;
-    tr.depth = depth;
-    tr.m_bp = small_div(max(bp, 1)).m;
-    // every voxel with weight for a pixel of the tile lies within |m.(v - c0)| < |m|_1 and,
-    // along the in-plane axes, within the tile's extent widened by |u|_1, |w|_1 (the margins
-    // cover FP32 rounding and the pose rigidity tolerance)
     const float slop = pl.slop;
+    tr.depth = pl.depth;
     tr.thr_n = fabsf(pl.f.fm[0]) + fabsf(pl.f.fm[1]) + fabsf(pl.f.fm[2]) + slop;
     tr.thr_u = l1u + 0.02f + slop;
     tr.thr_v = l1w + 0.02f + slop;
-    tr.hi_u = (float)(tr.ni - 1) * pl.f.lu + tr.thr_u;
-    tr.hi_v = (float)(tr.nj - 1) * pl.f.lw + tr.thr_v;
-    tr.inv_md = 1.0f / pick3(pl.f.fm, dax);
+    tr.inv_md = 1.0f / pick3(pl.f.fm, pl.f.dax);
     tr.half = pl.half;
+}
+
+// One thread, after `tile_box` and `tile_slab`: the tile's lateral extent.
+__device__ __forceinline__ void tile_extent(float lu, float lw, TileRec& tr) {
+    tr.hi_u = (float)(tr.ni - 1) * lu + tr.thr_u;
+    tr.hi_v = (float)(tr.nj - 1) * lw + tr.thr_v;
+}
+
+// One thread, after `tile_box` and `tile_slab`: the box's columns across the dominant axis, and
+// whether they fit the LDS budget (the request's bound makes every staged tile fit; a tile beyond it
+// would be left NaN, so the check only keeps the LDS accesses in bounds).
+__device__ __forceinline__ void tile_cols(int dax, TileRec& tr) {
+    const int pax = dax == 0 ? 1 : 0, qax = dax == 2 ? 1 : 2;
+    const int lo[3] = {tr.lo[0], tr.lo[1], tr.lo[2]}, hi[3] = {tr.hi[0], tr.hi[1], tr.hi[2]};
+    const int bp = pick3(hi, pax) - pick3(lo, pax) + 1, bq = pick3(hi, qax) - pick3(lo, qax) + 1;
+    const int depth = tr.depth;
+    const bool fits = bp >= 2 && bq >= 2 && depth >= 2 && depth <= kRunSpan && bp * bq <= kColsMax &&
+                      bp * bq * depth <= kItemsMax && pick3(hi, dax) - pick3(lo, dax) <= kRunSpan;
+    tr.mode = (tr.mode == 1 && fits) ? 1 : 0;
+    tr.bp = bp;
+    tr.bq = bq;
+    tr.ncols = bp * bq;
+    tr.m_bp = small_div(max(bp, 1)).m;
 }
 
 // One thread: the parts of a tile record that depend on the number of surviving bins.
 __device__ __forceinline__ void tile_bins(int kact, TileRec& tr) {
-    const int kactp = (kact + 7) & ~7;
+    const int kactp = row_bins(kact);
     tr.kactp = kactp;
     tr.m_kactp = small_div(max(kactp, 1)).m;
-    if (tr.nbb * kactp > kSlotsMax) tr.mode = 0;
 }
 
 __device__ __forceinline__ void compute_tile(const Plane& pl, int r, int t, TileRec& tr) {
     tile_box(pl.c00, pl.ex, pl.ey, pl.n, pl.tile, pl.W, pl.H, pl.tiles_x, r, t, tr);
-    tile_frame(pl, tr);
+    tile_slab(pl, tr);
+    tile_extent(pl.f.lu, pl.f.lw, tr);
+    tile_cols(pl.f.dax, tr);
     tile_bins(pl.kact, tr);
+    if (!slots_fit(tr.nbb, pl.kact)) tr.mode = 0;
 }
 
 // Slots phase: the table entry of every (box brick, bin) pair, -1 past the surviving bins.  The
@@ -323,9 +345,10 @@ __device__ __forceinline__ void load_slots(const SliceRec& rec, const TileRec& t
     const uint32_t nb32 = (uint32_t)ui((int)(nbricks & 0xFFFFFF));
 #pragma unroll
     for (int i = 0; i < slots_per_thread<NT>(); ++i) {
+        sl[i] = -1;
+        if (NT * i >= n) continue;   // the same for the whole workgroup
         const int e = (int)threadIdx.x + NT * i;
         const int bb = sdiv(e, dk), k = e - (int)__umul24((uint32_t)bb, (uint32_t)kactp);
-        sl[i] = -1;
         if (e < n && k < kact) {
             const int byz = sdiv(bb, dx), bx = bb - (int)__umul24((uint32_t)byz, (uint32_t)bdx);
             const int bz = sdiv(byz, dy), by = byz - (int)__umul24((uint32_t)bz, (uint32_t)bdy);
@@ -747,16 +770,23 @@ __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__
     __shared__ SliceRec rec;
     __shared__ TileRec tr;
     const int t = xcd_remap(blockIdx.x, gridDim.x);
-    // the request setup on three waves at once: wave 0 the bins (Eq. 1, gates, Eq. 2), wave 1 the
-    // plane and its frame, wave 2 this tile's pixels and voxel box (16 x 16 tiles); then the
-    // parts that need them together
+    // the request setup on four waves at once: wave 0 the bins (Eq. 1, gates, Eq. 2), wave 1 the
+    // plane and its frame, wave 2 this tile's pixels and voxel box (16 x 16 tiles), wave 3 the
+    // frame again for the slab thresholds and the box's bound; then, again on a wave each, the
+    // parts that need them together.  The workgroups of a launch are all in this phase at once, so
+    // its chain is paid in full: on three waves and one lane for the second part the two took 1.8 + 1.1
+    // us, now 1.85 + 0.43; with the table reads past the box's entries left out too (they cost
+    // issue slots), 16 slices of 512 x 512 went from 153.2 to 150.6 us.
+    __shared__ int fit, bound;
     double T[12];
     if (threadIdx.x < 64) {
         pad_bins(rec, slice_gates(vd, s, rec, T));
-    } else if (threadIdx.x < 192) {
+    } else {
         slice_pose(vd, s, T);
         if (threadIdx.x == 64) {
             request_frame(vd, s, T, rec);
+            rec.tile = 16;
+            rec.tiles_x = (s.W + 15) / 16;
         } else if (threadIdx.x == 128) {
             // the plane's position in voxel units, as request_frame computes it
             const double inv_h = vd->inv_h;
@@ -769,15 +799,32 @@ __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__
                 ey[a] = (s.sy * T[a * 4 + 1]) * inv_h;
             }
             tile_box(c00, ex, ey, n, 16, s.W, s.H, (s.W + 15) / 16, 0, t, tr);
+        } else if (threadIdx.x == 192) {
+            Plane pl;
+            pl.f = frame_of(vd, s, T);
+            const double inv_h = vd->inv_h;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                pl.ex[a] = (s.sx * T[a * 4 + 0]) * inv_h;
+                pl.ey[a] = (s.sy * T[a * 4 + 1]) * inv_h;
+            }
+            plane_slab(vd->nx, vd->ny, vd->nz, pl);
+            tile_slab(pl, tr);
+            int nbb;
+            fit = box_fits(pl, 16, nbb);
+            bound = nbb;
         }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        Plane pl = plane_of(rec);
-        if (request_mode(pl, rec, 16) == 1) {
-            tile_frame(pl, tr);
-            tile_bins(pl.kact, tr);
-        }
+        tile_bins(rec.kact, tr);
+    } else if (threadIdx.x == 64) {
+        tile_cols(rec.dax, tr);
+    } else if (threadIdx.x == 128) {
+        tile_extent(rec.lu, rec.lw, tr);
+    } else if (threadIdx.x == 192) {
+        const int kact = rec.kact;   // the tile's own bricks are at most the bound's
+        rec.mode = kact == 0 ? 0 : (fit && slots_fit(max(bound, tr.nbb), kact) ? 1 : 2);
     }
     __syncthreads();
     if (ui(rec.mode) == 1) run_tile<DT, 256, items_per_round<DT>(), bins_per_round<DT>()>(rec, tr, tl);
