@@ -2,7 +2,7 @@
 // Fig. 2): the trilinear cell of every pixel, each cell voxel blended over the direction bins
 // that pass the angular gates.
 //
-// The per-request part runs on the device in FP64 (`request_setup`, one wave): the slice pose
+// The per-request part runs on the device in FP64 (`slice_gates`, `request_frame`): the slice pose
 // T = P.C, Eq. 1 for every bin, the two gates and Eq. 2 for the survivors, the plane frame in
 // voxel units, and the choice of tile edge.  A request is then cut into square tiles of output
 // pixels, each with a record of its voxel box (`compute_tile`).  One workgroup takes one
@@ -23,8 +23,8 @@
 // A single reslice launches one workgroup per 16 x 16 tile; each workgroup evaluates the
 // request setup and its tile's record itself, since no other memory holds them: the bins on one
 // wave and the plane and tile geometry on another, at the same time.  A batch
-// runs the request setup once per request and the tile records once per tile (`k_tiles_setup`:
-// one workgroup per request, one thread per tile; it also appends the units to a list), then one
+// runs the request setup and the tile records in a pass of its own (`k_tiles_setup`: a few
+// workgroups per request, one thread per tile; it also appends the units to a list), then one
 // persistent kernel over all staged units (`k_tiles`), which reads both records through scalar
 // loads, with tiles of 32 x 32 pixels wherever their voxel box fits the LDS budget.  The
 // per-voxel and per-pixel arithmetic does not depend on the tile, so a request gives the same
@@ -138,12 +138,6 @@ __device__ __forceinline__ bool box_fits(const Plane& pl, int T, int& nbb) {
 __device__ __forceinline__ int row_bins(int kact) { return (kact + 7) & ~7; }
 __device__ __forceinline__ bool slots_fit(int nbb, int kact) { return nbb * row_bins(kact) <= kSlotsMax; }
 
-// Does a T x T tile of this request fit the LDS budget wherever it falls?
-__device__ __forceinline__ bool tile_fits(const Plane& pl, int T) {
-    int nbb;
-    return box_fits(pl, T, nbb) && slots_fit(nbb, pl.kact);
-}
-
 // The slab of a tile from the plane's frame: voxels with |m.(v - c0)| < |m|_1 (plus slop for FP32
 // rounding of coordinates up to the grid's size) form runs of at most ceil(2 half) voxels along dax.
 __device__ __forceinline__ void plane_slab(int nx, int ny, int nz, Plane& pl) {
@@ -188,39 +182,18 @@ __device__ __forceinline__ Plane request_frame(const VolDev* __restrict__ vd, co
     return pl;
 }
 
-// One lane, once the frame and the surviving bins are known: the mode and the tile edge.
-__device__ __forceinline__ int request_mode(Plane& pl, SliceRec& rec, int max_tile) {
-    const int kact = pl.kact;
-    int mode = kact > 0 ? 2 : 0, tile = 16;
-    if (kact > 0) {
-        if (max_tile >= kTileBig && tile_fits(pl, kTileBig)) {
-            mode = 1;
-            tile = kTileBig;
-        } else if (tile_fits(pl, 16)) {
-            mode = 1;
-        }
+// One lane: what the box bounds need of the plane, its frame and slab and the voxel steps per pixel.
+__device__ __forceinline__ Plane plane_bounds(const VolDev* __restrict__ vd, const SliceArgs& s, const double T[12]) {
+    Plane pl;
+    pl.f = frame_of(vd, s, T);
+    const double inv_h = vd->inv_h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        pl.ex[a] = (s.sx * T[a * 4 + 0]) * inv_h;
+        pl.ey[a] = (s.sy * T[a * 4 + 1]) * inv_h;
     }
-    pl.tile = tile;
-    pl.tiles_x = (pl.W + tile - 1) / tile;
-    rec.mode = mode;
-    rec.tile = tile;
-    rec.tiles_x = pl.tiles_x;
-    rec.ntiles = pl.tiles_x * ((pl.H + tile - 1) / tile);
-    return mode;
-}
-
-// One wave: the per-request setup of a radius-1 reslice, in FP64 on the device, into `rec`.
-// Lane 0 returns the number of work units (tiles) of the request and its mode in *mode_out.
-__device__ int request_setup(const VolDev* __restrict__ vd, const SliceArgs& s, SliceRec& rec, int max_tile,
-                             int* mode_out) {
-    double T[12];
-    const int kact = slice_gates(vd, s, rec, T);
-    pad_bins(rec, kact);
-    if ((threadIdx.x & 63) != 0) return 0;
-    Plane pl = request_frame(vd, s, T, rec);
-    pl.kact = kact;
-    *mode_out = request_mode(pl, rec, max_tile);
-    return rec.ntiles;
+    plane_slab(vd->nx, vd->ny, vd->nz, pl);
+    return pl;
 }
 
 // One thread: the part of tile t's record that needs only the plane's position in voxel units
@@ -800,15 +773,7 @@ __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__
             }
             tile_box(c00, ex, ey, n, 16, s.W, s.H, (s.W + 15) / 16, 0, t, tr);
         } else if (threadIdx.x == 192) {
-            Plane pl;
-            pl.f = frame_of(vd, s, T);
-            const double inv_h = vd->inv_h;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                pl.ex[a] = (s.sx * T[a * 4 + 0]) * inv_h;
-                pl.ey[a] = (s.sy * T[a * 4 + 1]) * inv_h;
-            }
-            plane_slab(vd->nx, vd->ny, vd->nz, pl);
+            const Plane pl = plane_bounds(vd, s, T);
             tile_slab(pl, tr);
             int nbb;
             fit = box_fits(pl, 16, nbb);
@@ -831,43 +796,83 @@ __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__
     else direct_tile<DT>(rec, t);
 }
 
-// Batch setup: one workgroup per request.  Its first wave writes the request record, then every
-// thread writes the records of tiles (one at a time) when it stages them; the units are appended: staged tiles' records from the front
+// Batch setup: `split` workgroups per request, each evaluating the request's record on its waves (the
+// bins, the plane, and the box bounds of either tile edge at once) and writing its share of the
+// tiles' records, a tile per thread.  The units are appended: staged tiles' records from the front
 // of `tiles` (counts[0]), the other requests' units (request, tile) from the back of `units`
-// (counts[2]: entry k at cap - 1 - k), so that each kind runs in a kernel of its own.
+// (counts[2]: entry k at cap - 1 - k), so that each kind runs in a kernel of its own.  Latency bounds
+// it: with the record on one wave and lane and one workgroup per request, 4 requests of 512 x 512
+// took 15.0 us, now 7.8 us (64 requests 9.3 and 8.5).
 __global__ void __launch_bounds__(kSetupThreads) k_tiles_setup(const BatchReq* __restrict__ reqs,
                                                                SliceRec* __restrict__ recs, int2* __restrict__ units,
                                                                TileRec* __restrict__ tiles, int* __restrict__ counts,
-                                                               int cap) {
+                                                               int cap, int split) {
     __shared__ SliceRec rec;
-    __shared__ int sh[3];                 // units, mode, first entry of the request's units
-    const int nreq = counts[1];
-    for (int r = blockIdx.x; r < nreq; r += gridDim.x) {
+    __shared__ int fit[2], bound[2];      // tile edges kTileBig, 16
+    __shared__ int sh[3];                 // this workgroup's first and last unit, first entry of its units
+    const int n = counts[1] * split;
+    for (int b = blockIdx.x; b < n; b += gridDim.x) {
+        const int r = b / split, part = b - r * split;
+        const VolDev* __restrict__ vd = reqs[r].vol;
+        const SliceArgs& s = reqs[r].s;
+        double T[12];
         if (threadIdx.x < 64) {
-            int mode = 0;
-            int nt = request_setup(reqs[r].vol, reqs[r].s, rec, kTileBig, &mode);
-            if (threadIdx.x == 0) {
-                // a request with no surviving bin is filled with NaN in flat runs of kFillRun
-                // pixels (fewer units than its tiles), marked by a negative tile index
-                if (mode == 0) nt = (int)(((int64_t)reqs[r].s.W * reqs[r].s.H + kFillRun - 1) / kFillRun);
-                sh[0] = nt;
-                sh[1] = mode;
-                sh[2] = atomicAdd(counts + (mode == 1 ? 0 : 2), nt);
+            pad_bins(rec, slice_gates(vd, s, rec, T));
+        } else {
+            slice_pose(vd, s, T);
+            if (threadIdx.x == 64) {
+                request_frame(vd, s, T, rec);
+            } else if (threadIdx.x == 128 || threadIdx.x == 192) {
+                const int k = threadIdx.x == 128 ? 0 : 1;
+                const Plane pl = plane_bounds(vd, s, T);
+                int nbb;
+                fit[k] = box_fits(pl, k ? 16 : kTileBig, nbb);
+                bound[k] = nbb;
             }
         }
         __syncthreads();
-        const int nt = sh[0], mode = sh[1], base = sh[2];
-        {   // the record to global memory (the tile kernels read it)
+        if (threadIdx.x == 0) {
+            const int kact = rec.kact;
+            int mode = 0, tile = 16;
+            if (kact > 0) {
+                const bool big = fit[0] && slots_fit(bound[0], kact);
+                mode = big || (fit[1] && slots_fit(bound[1], kact)) ? 1 : 2;
+                tile = big ? kTileBig : 16;
+            }
+            rec.mode = mode;
+            rec.tile = tile;
+            rec.tiles_x = (s.W + tile - 1) / tile;
+            rec.ntiles = rec.tiles_x * ((s.H + tile - 1) / tile);
+            // a request with no surviving bin is filled with NaN in flat runs of kFillRun pixels
+            // (fewer units than its tiles), marked by a negative tile index
+            const int64_t nt = mode == 0 ? ((int64_t)s.W * s.H + kFillRun - 1) / kFillRun : rec.ntiles;
+            sh[0] = (int)(nt * part / split);
+            sh[1] = (int)(nt * (part + 1) / split);
+        }
+        __syncthreads();
+        const int mode = rec.mode, k0 = sh[0], k1 = sh[1];
+        int base = 0;
+        if (threadIdx.x == 0 && k1 > k0) base = atomicAdd(counts + (mode == 1 ? 0 : 2), k1 - k0);
+        // the addition is in flight while the record goes to global memory (the tile kernels read
+        // it) and the first tiles' records are computed
+        if (part == 0) {
             const int* src = reinterpret_cast<const int*>(&rec);
             int* dst = reinterpret_cast<int*>(recs + r);
             for (int w = threadIdx.x; w < (int)(sizeof(SliceRec) / sizeof(int)); w += kSetupThreads) dst[w] = src[w];
         }
+        const int k = k0 + (int)threadIdx.x;
+        TileRec tr;
+        const Plane pl = plane_of(rec);
+        if (mode == 1 && k < k1) compute_tile(pl, r, k, tr);
+        if (threadIdx.x == 0) sh[2] = base;
+        __syncthreads();
+        base = sh[2];
         if (mode == 1) {
-            const Plane pl = plane_of(rec);
-            for (int k = threadIdx.x; k < nt; k += kSetupThreads) compute_tile(pl, r, k, tiles[base + k]);
+            if (k < k1) tiles[base + k - k0] = tr;
+            for (int t = k + kSetupThreads; t < k1; t += kSetupThreads) compute_tile(pl, r, t, tiles[base + t - k0]);
         } else {
-            for (int k = threadIdx.x; k < nt; k += kSetupThreads)
-                units[cap - 1 - (base + k)] = make_int2(r, mode == 0 ? ~k : k);
+            for (int t = k; t < k1; t += kSetupThreads)
+                units[cap - 1 - (base + t - k0)] = make_int2(r, mode == 0 ? ~t : t);
         }
         __syncthreads();
     }
@@ -990,9 +995,12 @@ hipError_t launch_reslice_tile(const VolDev* vd, int dtype, const SliceArgs& s, 
 
 hipError_t launch_tiles_batch(int dtype, const BatchReq* reqs, SliceRec* recs, int2* units, TileRec* tiles,
                               int* counts, int nreq_max, int cap, hipStream_t stream) {
-    const int sgrid = nreq_max < 1024 ? (nreq_max > 0 ? nreq_max : 1) : 1024;
+    // workgroups per request: one for each 256 possible tiles, while there are CUs for two each
+    const int n = std::max(nreq_max, 1);
+    const int split = std::max(1, std::min(8, std::min(cap / n / kSetupThreads, 512 / n)));
+    const int sgrid = std::min(n * split, 1024);
     hipLaunchKernelGGL(k_tiles_setup, dim3(sgrid), dim3(kSetupThreads), 0, stream, reqs, recs, units, tiles, counts,
-                       cap);
+                       cap, split);
 #define L(D)                                                                                                   \
     hipLaunchKernelGGL(k_tiles<D>, dim3(tiles_grid<D>()), dim3(kThreadsBatch), 0, stream, recs, tiles, counts); \
     hipLaunchKernelGGL(k_tiles_direct<D>, dim3(1024), dim3(256), 0, stream, recs, units, counts, cap)
