@@ -13,7 +13,7 @@ from test_literal_gpu import _scene, _slice, _store
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("W,H,pv,R,shift", [(21, 18, 0.2, 1, 0.0), (33, 17, 0.5, 2, 2.0), (18, 16, 1.5, 3, 0.0),
+@pytest.mark.parametrize("W,H,pv,R,shift", [(21, 18, 0.2, 1, 0.0), (33, 17, 0.5, 2, 2.0), (18, 16, 1.5, 3, 0.0), (19, 17, 1.2, 2, 0.0),
                                             (17, 19, 6.0, 1, 1.0), (16, 16, 0.4, 1, 40.0)])
 def test_boxes_vs_oracle(W, H, pv, R, shift):
     import torch
