@@ -166,26 +166,17 @@ __device__ __forceinline__ void slice_frame(const VolDev* __restrict__ vd, const
     store_frame(frame_of(vd, s, T), sh);
 }
 
-// Wave 0 only: slice pose, Eq. 1 / thresholds / Eq. 2 per bin, survivors compacted, and the
-// plane frame (lane 0).  Returns the number of surviving bins; T receives the composed pose.
-__device__ __forceinline__ int slice_setup(const VolDev* __restrict__ vd, const SliceArgs& s, SetupLds& sh,
-                                           double T[12]) {
-    const int kact = slice_gates(vd, s, sh, T);
-    if ((threadIdx.x & 63) == 0) slice_frame(vd, s, T, sh);
-    return kact;
-}
-
 struct SlicePos {            // per-workgroup uniform position terms
     double t[3], e0[3], e1[3], o[3], inv_h, sx, sy;
 };
 
-__device__ __forceinline__ void load_pos(const VolDev* __restrict__ vd, const SetupLds& sh, const SliceArgs& s,
+__device__ __forceinline__ void load_pos(const VolDev* __restrict__ vd, const double T[12], const SliceArgs& s,
                                          SlicePos& q) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        q.t[a] = uniform_f64(sh.T[a * 4 + 3]);
-        q.e0[a] = uniform_f64(sh.T[a * 4 + 0]);
-        q.e1[a] = uniform_f64(sh.T[a * 4 + 1]);
+        q.t[a] = uniform_f64(T[a * 4 + 3]);
+        q.e0[a] = uniform_f64(T[a * 4 + 0]);
+        q.e1[a] = uniform_f64(T[a * 4 + 1]);
         q.o[a] = vd->origin[a];
     }
     q.inv_h = vd->inv_h;

@@ -59,10 +59,22 @@ constexpr int kBoxBricks = 511, kBoxEdge = 60;
 template <int DT, int R>
 struct WideLds {
     SetupLds sh;
+    int lat[3], len[3];                                      // the whole tile's lattice points
+    float c0[3];
     int nlist;
     alignas(16) int slot[WideLimits<R>::kSlots];             // [box brick][bin], rows of kactp
     float2 scale[DT == DARE_FP8_E4M3 ? WideLimits<R>::kSlots : 1];
     alignas(16) float pool[WideLimits<R>::kPool];
+};
+
+// x / d for 0 <= x < 2^20 through the hardware reciprocal: (x + 1/2) / d lies at least 1/(2 d) from a
+// whole number, further than the products' rounding (relative 2^-22) moves it.  One reciprocal to set
+// up, where the multiplier of an exact integer division takes some 25 instructions of every wave:
+// a piece divides by eight different numbers.
+struct FloatDiv {
+    float r, h;
+    __device__ __forceinline__ explicit FloatDiv(int d) : r(__builtin_amdgcn_rcpf((float)d)), h(0.5f * r) {}
+    __device__ __forceinline__ int operator()(int x) const { return (int)__builtin_fmaf((float)x, r, h); }
 };
 
 // Minimum over the four lanes of a quad.
@@ -148,10 +160,10 @@ __device__ __forceinline__ void list_cubes(const VolView& vv, const Piece& t, Wi
         c_n[a] = ((min(t.lo[a] + t.dim[a], vv.n[a]) - 1) >> 1) - c_lo[a] + 1;
     }
     const int n = c_n[0] * c_n[1] * c_n[2];
-    const SmallDiv dz = small_div(c_n[2]), dy = small_div(c_n[1]);
+    const FloatDiv dz(c_n[2]), dy(c_n[1]);
     for (int base = 0; base < n; base += NT) {
         const int e = base + (int)threadIdx.x;
-        const int exy = sdiv(e, dz), cx = sdiv(exy, dy);
+        const int exy = dz(e), cx = dy(exy);
         const int c[3] = {c_lo[0] + cx, c_lo[1] + exy - cx * c_n[1], c_lo[2] + e - exy * c_n[2]};
         float dn = 0.0f, du = 0.0f, dv = 0.0f;
 #pragma unroll
@@ -370,12 +382,12 @@ __device__ __forceinline__ void wide_piece(const VolView& vv, const SlicePos& q,
     // slots: the table entry of every (box brick, bin) pair, -1 past the surviving bins; a thread's
     // first read is in flight during the classification
     const int nsl = t.bdim[0] * t.bdim[1] * t.bdim[2] * kactp;
-    const SmallDiv dk = small_div(kactp), dx = small_div(t.bdim[0]), dy = small_div(t.bdim[1]);
+    const FloatDiv dk(kactp), dx(t.bdim[0]), dy(t.bdim[1]);
     auto slot_of = [&](int e) {
-        const int bb = sdiv(e, dk), k = e - bb * kactp;
+        const int bb = dk(e), k = e - bb * kactp;
         if (e >= nsl || k >= kact) return -1;
-        const int byz = sdiv(bb, dx), bx = bb - byz * t.bdim[0];
-        const int bz = sdiv(byz, dy), by = byz - bz * t.bdim[1];
+        const int byz = dx(bb), bx = bb - byz * t.bdim[0];
+        const int bz = dy(byz), by = byz - bz * t.bdim[1];
         const int64_t brick = ((int64_t)(t.blo[2] + bz) * vv.nby + (t.blo[1] + by)) * vv.nbx + (t.blo[0] + bx);
         return (int)global(vv.table)[(int64_t)L.sh.act_bin[k] * vv.nbricks + brick];
     };
@@ -399,9 +411,9 @@ __device__ __forceinline__ void wide_piece(const VolView& vv, const SlicePos& q,
     __syncthreads();
     {   // along d: V -> P1[q][p][g]
         const int nb = (ld + 3) >> 2, n = vp * vq * nb;
-        const SmallDiv db = small_div(nb);
+        const FloatDiv db(nb);
         for (int x = tid; x < n; x += NT) {
-            const int col = sdiv(x, db), b = x - col * nb, base = col * vd + 4 * b, left = vd - 1 - 4 * b;
+            const int col = db(x), b = x - col * nb, base = col * vd + 4 * b, left = vd - 1 - 4 * b;
             float2 o[4];
             taps4<R>([&](int j, float& num, float& den) {
                 const float v = V[base + min(j, left)];
@@ -417,9 +429,9 @@ __device__ __forceinline__ void wide_piece(const VolView& vv, const SlicePos& q,
     __syncthreads();
     {   // along p: P1 -> P2[q][gp][g]
         const int nb = (lp + 3) >> 2, n = vq * nb * ld;
-        const SmallDiv dl = small_div(ld), db = small_div(nb);
+        const FloatDiv dl(ld), db(nb);
         for (int x = tid; x < n; x += NT) {
-            const int r = sdiv(x, dl), g = x - r * ld, cq = sdiv(r, db), b = r - cq * nb;
+            const int r = dl(x), g = x - r * ld, cq = db(r), b = r - cq * nb;
             const int base = (cq * vp + 4 * b) * ld + g, left = vp - 1 - 4 * b;
             float2 o[4];
             taps4<R>([&](int j, float& num, float& den) {
@@ -435,9 +447,9 @@ __device__ __forceinline__ void wide_piece(const VolView& vv, const SlicePos& q,
     __syncthreads();
     {   // along q: P2 -> P3[gq][gp][g], in P1's place
         const int nb = (lq + 3) >> 2, plane = lp * ld, n = nb * plane;
-        const SmallDiv dp = small_div(plane);
+        const FloatDiv dp(plane);
         for (int x = tid; x < n; x += NT) {
-            const int b = sdiv(x, dp), g = x - b * plane, base = 4 * b * plane + g, left = vq - 1 - 4 * b;
+            const int b = dp(x), g = x - b * plane, base = 4 * b * plane + g, left = vq - 1 - 4 * b;
             float2 o[4];
             taps4<R>([&](int j, float& num, float& den) {
                 const float2 v = P2[base + min(j, left) * plane];
@@ -464,30 +476,48 @@ __device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const S
                                           int parts, WideLds<DT, R>& L) {
     const int ty = unit / s.tiles_x, tx = unit - ty * s.tiles_x;
     const int i0 = tx * kTile, j0 = ty * kTile;
-    {   // the bins on wave 0 and the plane's frame on wave 1, at once
+    const int ni = min(kTile, s.W - i0), nj = min(kTile, s.H - j0);
+    const VolView vv = view_of(vd);
+    SlicePos q;
+    {   // the bins on wave 0, the plane's frame on wave 1 and the tile's lattice points on wave 2, at once
         double T[12];
+        slice_pose(vd, s, T);
+        load_pos(vd, T, s, q);
         if (threadIdx.x < 64) {
             pad_bins(L.sh, slice_gates(vd, s, L.sh, T));
-        } else if (threadIdx.x < 128) {
-            slice_pose(vd, s, T);
-            if (threadIdx.x == 64) slice_frame(vd, s, T, L.sh);
+        } else if (threadIdx.x == 64) {
+            slice_frame(vd, s, T, L.sh);
+        } else if (threadIdx.x >= 128 && threadIdx.x < 192) {
+            int lat[3], len[3];
+            float c0[3];
+            tile_cells(q, i0, j0, i0 + ni - 1, j0 + nj - 1, lat, len, c0);
+            if (threadIdx.x == 128) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    L.lat[a] = lat[a];
+                    L.len[a] = len[a];
+                    L.c0[a] = c0[a];
+                }
+            }
         }
     }
     __syncthreads();
     const int kact = ui(L.sh.kact), kactp = (kact + 7) & ~7, dax = ui(L.sh.dax);
     if (kact == 0) {
-        if (part == 0) nan_piece<NT>(s, i0, j0, min(kTile, s.W - i0), min(kTile, s.H - j0));
+        if (part == 0) nan_piece<NT>(s, i0, j0, ni, nj);
         return;
     }
-    SlicePos q;
-    load_pos(vd, L.sh, s, q);
-    const VolView vv = view_of(vd);
     Piece t;
     t.i0 = i0;
     t.j0 = j0;
-    t.ni = min(kTile, s.W - i0);
-    t.nj = min(kTile, s.H - j0);
-    tile_cells(q, i0, j0, i0 + t.ni - 1, j0 + t.nj - 1, t.lat, t.len, t.c0);
+    t.ni = ni;
+    t.nj = nj;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        t.lat[a] = ui(L.lat[a]);
+        t.len[a] = ui(L.len[a]);
+        t.c0[a] = uf(L.c0[a]);
+    }
     if (wide_fits<R>(t.len, dax, kactp)) {
         if (part == 0) wide_piece<DT, R, NT>(vv, q, s, t, kTile, dax, kact, kactp, L);
         return;
