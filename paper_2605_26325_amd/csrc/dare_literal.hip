@@ -328,6 +328,10 @@ __device__ inline float blend_range(const LitSlice& s, const double c[3], const 
 // the result is the same as summing per pixel.  A tile whose box exceeds kTileBox voxels (coarse
 // output pitch, large radius) does sum per pixel; the launch takes tiles of 8 or 4 pixels square
 // where 16 would (`tile_shift`): all the threads then sum the voxels, and a part of them has pixels.
+// CUBE: the box reading at R = 1, where a pixel inside the grid takes a whole 3 x 3 x 3 cube (its reads
+// unrolled: 23.3 -> 20.7 us for a 512 x 512 slice; in one kernel with the other readings they made
+// those 2 % slower).
+template <bool CUBE>
 __global__ void __launch_bounds__(256) k_lit_reslice_tiled(SampleDev d, LitSlice s, int tiles_x,
                                                            int shift) {
     extern __shared__ float lut_s[];
@@ -416,6 +420,19 @@ __global__ void __launch_bounds__(256) k_lit_reslice_tiled(SampleDev d, LitSlice
     }
     __syncthreads();
     if (!inside) return;
+    if (CUBE && reach && hi[0] - lo[0] == 2 && hi[1] - lo[1] == 2 && hi[2] - lo[2] == 2) {
+        // the sums are exact in any order
+        const double2* at = sums + ((lo[2] - b0[2]) * ny + (lo[1] - b0[1])) * nx + (lo[0] - b0[0]);
+        double num = 0.0, den = 0.0;
+#pragma unroll
+        for (int v = 0; v < 27; ++v) {
+            const double2 x = at[((v / 9) * ny + (v / 3) % 3) * nx + v % 3];
+            den += x.x;
+            num += x.y;
+        }
+        s.out[p] = den > 0.0 ? (float)(num / den) : __builtin_nanf("");
+        return;
+    }
     s.out[p] = !reach ? __builtin_nanf("")
                       : blend_range(s, c, lo, hi, [&](int vx, int vy, int vz, double& sw, double& swi) {
                             const double2 q = sums[((vz - b0[2]) * ny + (vy - b0[1])) * nx + (vx - b0[0])];
@@ -644,7 +661,8 @@ dare_status dare_samples_reslice(const dare_samples* st, const dare_params* p, c
     const int shift = tile_shift(s, 1.0 / st->g.spacing_mm), edge = 1 << shift;
     const int tiles_x = (s.W + edge - 1) >> shift;
     const int64_t tiles = (int64_t)tiles_x * ((s.H + edge - 1) >> shift);
-    hipLaunchKernelGGL(k_lit_reslice_tiled, dim3((unsigned)tiles), dim3(256), lds, stream, st->d, s, tiles_x, shift);
+    hipLaunchKernelGGL(s.mode == DARE_LITERAL_BOX && s.R == 1 ? k_lit_reslice_tiled<true> : k_lit_reslice_tiled<false>,
+                       dim3((unsigned)tiles), dim3(256), lds, stream, st->d, s, tiles_x, shift);
     return hip_status(hipGetLastError());
 }
 
