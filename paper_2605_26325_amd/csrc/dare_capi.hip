@@ -1,6 +1,6 @@
 // C ABI: argument validation, arena layout, reconstruction orchestration,
 // reslice launches and the batched request planner.  Host code only; the
-// kernels live in dare_compound.hip and dare_reslice.hip.
+// kernels live in dare_compound.hip, dare_tiles.hip and dare_reslice_rs.hip.
 #include <math.h>
 #include <string.h>
 

@@ -308,12 +308,13 @@ __device__ __forceinline__ void pixels_wide(const VolView& vv, const SlicePos& q
         float val = __builtin_nanf("");
         if (c[0] > -(double)R && c[0] < (double)(vv.n[0] - 1 + R) && c[1] > -(double)R &&
             c[1] < (double)(vv.n[1] - 1 + R) && c[2] > -(double)R && c[2] < (double)(vv.n[2] - 1 + R)) {
-            // per axis: the nearer corner (base) and the weight w <= 1/2 of the other one, from FP64
-            // (w is positive where FP64's is).  lerp(base, other) = base + w (other - base) is then
-            // positive whenever a corner with positive weight is, and loses nothing where both
-            // corners hold the same (D away from the borders).
+            // per axis: the nearer corner (base) and the weight w <= 1/2 of the other one.
+            // lerp(base, other) = base + w (other - base) is then positive whenever a corner with
+            // positive weight is, and loses nothing where both corners hold the same (D away from the
+            // borders).  The first axis in FP32, the others and the quotient in FP64, so that the
+            // result is rounded once more only.
             int b[3], step[3];
-            float w[3];
+            double w[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const double fl = floor(c[a]), f = c[a] - fl;
@@ -321,21 +322,30 @@ __device__ __forceinline__ void pixels_wide(const VolView& vv, const SlicePos& q
                 // the cell lies in the box; the clamp only keeps the LDS reads in bounds
                 b[a] = min(max((int)fl - t.lat[a], 0), t.len[a] - 2) + (up ? 1 : 0);
                 step[a] = up ? -1 : 1;
-                w[a] = (float)(up ? fl + 1.0 - c[a] : f);
+                w[a] = up ? fl + 1.0 - c[a] : f;
             }
             const float2* cell = P3 + (b[QAX] * lp + b[PAX]) * ld + b[DAX];
             const int sd = step[DAX], sp = step[PAX] * ld, sq = step[QAX] * lp * ld;
             auto lerp = [](float2 lo, float2 hi, float x) {
                 return make_float2(__builtin_fmaf(x, hi.x - lo.x, lo.x), __builtin_fmaf(x, hi.y - lo.y, lo.y));
             };
-            float2 r[4];
+            double2 r[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float2* e = cell + (k >> 1) * sq + (k & 1) * sp;
-                r[k] = lerp(e[0], e[sd], w[DAX]);
+                const float2 x = lerp(e[0], e[sd], (float)w[DAX]);
+                r[k] = make_double2((double)x.x, (double)x.y);
             }
-            const float2 nd = lerp(lerp(r[0], r[1], w[PAX]), lerp(r[2], r[3], w[PAX]), w[QAX]);
-            if (nd.y > 0.0f) val = nd.x / nd.y;
+            auto lerp2 = [](double2 lo, double2 hi, double x) {
+                return make_double2(__builtin_fma(x, hi.x - lo.x, lo.x), __builtin_fma(x, hi.y - lo.y, lo.y));
+            };
+            const double2 nd = lerp2(lerp2(r[0], r[1], w[PAX]), lerp2(r[2], r[3], w[PAX]), w[QAX]);
+            if (nd.y > 1e-30) {   // the quotient from an FP32 reciprocal and one correction
+                const double inv = (double)(1.0f / (float)nd.y), q0 = nd.x * inv;
+                val = (float)__builtin_fma(__builtin_fma(-q0, nd.y, nd.x), inv, q0);
+            } else if (nd.y > 0.0) {   // beyond the FP32 reciprocal's range
+                val = (float)(nd.x / nd.y);
+            }
         }
         out[(size_t)j * s.W + i] = val;
     }

@@ -66,3 +66,31 @@ def test_wide_radius_pieces_vs_oracle(R, dtype):
     torch.cuda.synchronize()
     for k, (o, x) in enumerate(zip(outs, alone)):
         assert torch.equal(o.view(torch.int32), x.view(torch.int32)), f"R={R} {dtype} case {k}: batched differs"
+
+
+@pytest.mark.parametrize("R", [2, 5])
+def test_only_a_far_corner_assigned(R):
+    """Pixels a rounding error off a lattice point on every axis, where the only valid voxels lie R
+    away on the far side: FP64 weights of about 1e-39 to 1e-48, whose quotient is the voxel's value."""
+    import torch
+
+    import paper_2605_26325_amd as dare
+    note(f"far corner, R={R}")
+    dims, h, N = (24, 24, 24), 1.0, 24
+    S, C = np.zeros((1, N, N, N), np.int64), np.zeros((1, N, N, N), np.int64)
+    S[0, 12, 12, 12], C[0, 12, 12, 12] = 3 * 97, 3
+    prm = Params(radius_vox=R)
+    calib = np.eye(4)
+    origin = np.zeros(3)
+    vol = make_volume(origin, h, dims, calib, prm)
+    upload_grid(vol, S, C, np.array([[0.0, 0.0, 1.0]]), np.array([[1.0, 0.0, 0.0]]))
+    a, c = quant.storage(S, C, "fp32")
+    for eps in (1e-9, 1e-13, 1.8e-15):
+        T = np.eye(4)
+        T[:3, 3] = 12.0 + R - eps          # pixel (0, 0): R - eps from the voxel on every axis
+        W = H = 3
+        p = (1.0, 1.0)
+        out = vol.reslice(T, W, H, p).cpu().numpy()
+        ref = reslice.reslice(a, c, origin, h, np.array([[0.0, 0.0, 1.0]]), np.array([[1.0, 0.0, 0.0]]), calib, T, W, H, p, prm)
+        assert not np.isnan(ref[0, 0])
+        assert_parity(out, ref, what=f"R={R} eps={eps}")
