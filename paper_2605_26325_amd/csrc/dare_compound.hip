@@ -173,12 +173,18 @@ __global__ void k_compose_frames(VolDev* vd, const float* __restrict__ poses, in
 // final, the opener takes the next bin, and the entries after it test that one bin more.  Identical
 // results in n / 512 passes over the codebook and at most max_bins tests of one bin.  Bound: the
 // chain of FP64 dot products and barriers of one workgroup; 2400 (frame, sector) entries that open
-// 64 bins take 98 us, against 283 with the whole codebook tested again after every opener.
+// 64 bins take 59 us, against 283 with the whole codebook tested again after every opener and 98
+// with the opener found by an LDS minimum over all lanes and its vectors read after a second barrier.
 constexpr int kAssign = 512;
 __global__ void __launch_bounds__(kAssign) k_assign_bins(VolDev* vd, int n, int K0) {
     __shared__ double rep[kMaxBins][6];   // per bin: representative normal, then in-plane axis
-    __shared__ int s_first[2], s_sat;     // the chunk's next opener: one in use, one being reset
+    // per wave: its first entry that would open a bin (kAssign: none) and that entry's vectors; one
+    // copy is written while the other may still be read, so a round has one barrier
+    __shared__ int s_first[2][kAssign / 64];
+    __shared__ double s_cand[2][kAssign / 64][6];
+    __shared__ int s_sat;
     const int tid = threadIdx.x;
+    const int wave = tid >> 6;
     if (tid < K0) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -186,10 +192,7 @@ __global__ void __launch_bounds__(kAssign) k_assign_bins(VolDev* vd, int n, int 
             rep[tid][3 + a] = vd->rep_x[tid][a];
         }
     }
-    if (tid == 0) {
-        s_first[0] = s_first[1] = kAssign;
-        s_sat = vd->st.saturated;
-    }
+    if (tid == 0) s_sat = vd->st.saturated;
     int K = K0, turn = 0;
     const double ct = vd->cos_tol;
     const int kmax = vd->max_bins;
@@ -207,9 +210,9 @@ __global__ void __launch_bounds__(kAssign) k_assign_bins(VolDev* vd, int n, int 
                 xf[a] = fd->xh[a];
             }
         }
-        auto test = [&](int b) {   // strict > keeps the lowest index on ties
-            const double rn[3] = {rep[b][0], rep[b][1], rep[b][2]};
-            const double rx[3] = {rep[b][3], rep[b][4], rep[b][5]};
+        auto test = [&](int b, const double* r) {   // strict > keeps the lowest index on ties
+            const double rn[3] = {r[0], r[1], r[2]};
+            const double rx[3] = {r[3], r[4], r[5]};
             const double dn = dot3(nf, rn);
             const double di = fabs(dot3(xf, rx));
             const double sc = dn + di;
@@ -222,13 +225,22 @@ __global__ void __launch_bounds__(kAssign) k_assign_bins(VolDev* vd, int n, int 
                 best = b;
             }
         };
-        for (int b = 0; b < K; ++b) test(b);
-        for (int done = 0;; ) {    // entries before `done` are final
-            if (f < n && tid >= done && best < 0 && K < kmax) atomicMin(&s_first[turn], tid);
+        for (int b = 0; b < K; ++b) test(b, rep[b]);
+        for (;; turn ^= 1) {   // every entry before the round's opener is final
+            const uint64_t open = __ballot(f < n && best < 0 && K < kmax);
+            const int first = open ? wave * 64 + __builtin_ctzll(open) : kAssign;
+            if ((tid & 63) == 0) s_first[turn][wave] = first;
+            if (tid == first) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    s_cand[turn][wave][a] = nf[a];
+                    s_cand[turn][wave][3 + a] = xf[a];
+                }
+            }
             __syncthreads();
-            const int p = s_first[turn];
-            turn ^= 1;
-            if (tid == 0) s_first[turn] = kAssign;
+            int p = kAssign;
+#pragma unroll
+            for (int w = 0; w < kAssign / 64; ++w) p = min(p, s_first[turn][w]);
             if (p == kAssign) break;
             if (tid == p) {
                 best = K;
@@ -238,11 +250,10 @@ __global__ void __launch_bounds__(kAssign) k_assign_bins(VolDev* vd, int n, int 
                     rep[K][3 + a] = xf[a];
                 }
             }
-            __syncthreads();
-            if (tid > p) test(K);
+            if (tid > p) test(K, s_cand[turn][p >> 6]);
             ++K;
-            done = p + 1;
         }
+        turn ^= 1;   // the copy just read stays as it is through the next chunk's first round
         __syncthreads();
         if (f < n) {
             vd->frame_bin[f] = best >= 0 ? best : any;
