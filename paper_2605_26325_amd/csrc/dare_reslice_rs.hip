@@ -191,7 +191,8 @@ __device__ __forceinline__ void list_cubes(const VolView& vv, const Piece& t, Wi
 // Voxels phase, second part: the listed cubes' voxels, eight lanes per cube (so a wave reads whole
 // lines of a bin), their surviving bins gathered and blended into V_v, NaN when none holds a
 // sample.  U voxels of NB bins per thread and round: their pair loads are all issued before any is
-// used; a pair with no slot is skipped and adds nothing.
+// used; a pair with no slot is skipped and adds nothing.  With one surviving bin its weight cancels:
+// V_v is the stored value itself, unrounded and whatever the weight (which may underflow).
 template <int DT, int R, int NT>
 __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, int dax, WideLds<DT, R>& L,
                                             const int* list, float* V, int kact, int kactp) {
@@ -261,6 +262,17 @@ __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, i
                     const float wc = w * c;
                     A[u] = __builtin_fmaf(wc, a, A[u]);
                     B[u] = B[u] + wc;
+                }
+            }
+            if (kact == 1) {   // the same for the whole workgroup; the pair is the row's first
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float2 sc = make_float2(0.0f, 0.0f);
+                    if constexpr (DT == DARE_FP8_E4M3) sc = L.scale[row[u]];
+                    float a, c;
+                    PT::decode(pr[u][0], sc, a, c);
+                    A[u] = a;
+                    B[u] = c > 0.0f ? 1.0f : 0.0f;
                 }
             }
         }
