@@ -191,8 +191,8 @@ __device__ __forceinline__ void list_cubes(const VolView& vv, const Piece& t, Wi
 // Voxels phase, second part: the listed cubes' voxels, eight lanes per cube (so a wave reads whole
 // lines of a bin), their surviving bins gathered and blended into V_v, NaN when none holds a
 // sample.  U voxels of NB bins per thread and round: their pair loads are all issued before any is
-// used; a pair with no slot is skipped and adds nothing.  With one surviving bin its weight cancels:
-// V_v is the stored value itself, unrounded and whatever the weight (which may underflow).
+// used; a pair with no slot is skipped and adds nothing.  With one surviving bin its weight cancels
+// and is taken as 1 (it may underflow); V_v is then the stored value itself, unrounded.
 template <int DT, int R, int NT>
 __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, int dax, WideLds<DT, R>& L,
                                             const int* list, float* V, int kact, int kactp) {
@@ -202,6 +202,7 @@ __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, i
     const gptr<const T> data = global((const T*)vv.data);
     const uint32_t cap = (uint32_t)ui((int)vv.cap);
     const int nvox = 8 * ui(L.nlist);
+    const bool one = kact == 1;
     // V's strides per axis, the lane's place in a cube, and the in-grid part of the box
     const int pax = dax == 0 ? 1 : 0;
     const int vd = pick3(t.dim, dax), vdp = vd * pick3(t.dim, pax);
@@ -216,7 +217,7 @@ __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, i
     for (int base = 0; base < nvox; base += U * NT) {
         int row[U], loc[U], vi[U];
         bool ok[U];
-        float A[U], B[U];
+        float A[U], B[U], first[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = base + u * NT + (int)threadIdx.x;
@@ -228,7 +229,7 @@ __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, i
             vi[u] = x * str[0] + y * str[1] + z * str[2];
             row[u] = (int)__umul24((ent >> 6) & 511, (uint32_t)kactp);
             loc[u] = (int)(ent & 63) << 3 | ((int)threadIdx.x & 7);
-            A[u] = B[u] = 0.0f;
+            A[u] = B[u] = first[u] = 0.0f;
         }
         for (int k0 = 0; k0 < kact; k0 += NB) {
             int sl[U][NB];
@@ -259,26 +260,16 @@ __device__ __forceinline__ void gather_wide(const VolView& vv, const Piece& t, i
                     if constexpr (DT == DARE_FP8_E4M3) sc = L.scale[row[u] + k0 + g];
                     float a, c;
                     PT::decode(pr[u][g], sc, a, c);
+                    if (g == 0) first[u] = a;
                     const float wc = w * c;
                     A[u] = __builtin_fmaf(wc, a, A[u]);
                     B[u] = B[u] + wc;
                 }
             }
-            if (kact == 1) {   // the same for the whole workgroup; the pair is the row's first
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float2 sc = make_float2(0.0f, 0.0f);
-                    if constexpr (DT == DARE_FP8_E4M3) sc = L.scale[row[u]];
-                    float a, c;
-                    PT::decode(pr[u][0], sc, a, c);
-                    A[u] = a;
-                    B[u] = c > 0.0f ? 1.0f : 0.0f;
-                }
-            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (ok[u]) V[vi[u]] = B[u] > 0.0f ? A[u] / B[u] : __builtin_nanf("");
+            if (ok[u]) V[vi[u]] = B[u] > 0.0f ? (one ? first[u] : A[u] / B[u]) : __builtin_nanf("");
     }
 }
 
@@ -506,7 +497,9 @@ __device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const S
         slice_pose(vd, s, T);
         load_pos(vd, T, s, q);
         if (threadIdx.x < 64) {
-            pad_bins(L.sh, slice_gates(vd, s, L.sh, T));
+            const int n = slice_gates(vd, s, L.sh, T);
+            pad_bins(L.sh, n);
+            if (n == 1 && threadIdx.x == 0) L.sh.act_w[0] = 1.0f;   // it cancels
         } else if (threadIdx.x == 64) {
             slice_frame(vd, s, T, L.sh);
         } else if (threadIdx.x >= 128 && threadIdx.x < 192) {
