@@ -14,12 +14,12 @@ struct BatchReq {
     SliceArgs s;
 };
 
-// Batch header at the start of a workspace: int32 counts {units, requests, units at the list's
-// back, workgroups per unit (radii above 1)}, then the radius-1 tile kernel's claim counter of each of the 8 XCDs, each on a
-// 256-byte line of its own (claims[x][0]: counters that share a line serialise each other's
-// atomics).  At radius 1 the units are appended on the device, so counts[0] and counts[2] must be
-// uploaded as 0, and so must the claims; at other radii the host uploads the unit list and its
-// length in counts[0].  The kernels address the header as int32 words from counts.
+// Batch header at the start of a workspace: int32 counts, then the radius-1 tile kernel's claim
+// counter of each of the 8 XCDs, each on a 256-byte line of its own (claims[x][0]: counters that
+// share a line serialise each other's atomics).  Radius 1: counts {units, requests, units at the
+// list's back, 0}; the units are appended on the device, so counts[0] and counts[2] must be
+// uploaded as 0, and so must the claims.  Other radii: {units, requests, units at the list's front
+// that take several workgroups, how many}, uploaded with the unit list.  The kernels address the header as int32 words from counts.
 constexpr int kClaimStride = 64;          // int32 words between two XCDs' claim counters
 struct BatchHeader {
     int32_t counts[4];

@@ -192,7 +192,21 @@ int volume_dtype(const dare_volume* v) { return v->dtype; }
 int volume_radius(const dare_volume* v) { return (int)v->p.radius_vox; }
 int volume_device_id(const dare_volume* v) { return v->device; }
 uint64_t volume_arena_size(const dare_volume* v) { return v->arena_bytes; }
-double volume_spacing(const dare_volume* v) { return v->g.spacing_mm; }
+void add_staged_units(const dare_volume* v, const dare_slice_spec* s, int r, StagedUnits<int2>& u) {
+    double T[16];
+    compose_host(s->probe_pose, v->g.calib, T);
+    PlaneView w;
+    for (int a = 0; a < 3; ++a) {
+        w.c00[a] = (T[a * 4 + 3] - v->host.origin[a]) * v->host.inv_h;
+        w.ex[a] = s->pitch_mm[0] * T[a * 4 + 0] * v->host.inv_h;
+        w.ey[a] = s->pitch_mm[1] * T[a * 4 + 1] * v->host.inv_h;
+        w.n[a] = v->g.dims[a];
+    }
+    w.W = s->width;
+    w.H = s->height;
+    w.reach = v->p.radius_vox;
+    u.add(w, r, pitch_vox(v, s));
+}
 dare_status check_slice_spec(const dare_slice_spec* s) { return check_spec(s); }
 bool rigid_pose(const double* M) { return rigid(M); }
 void compose_pose(const double* P, const double* C, double* T) { compose_host(P, C, T); }
@@ -204,8 +218,7 @@ namespace {
 
 struct Group {
     std::vector<BatchReq> reqs;
-    std::vector<int2> units;      // radii above 1: built here; radius 1: built on the device
-    double pitch = 0.0;           // largest output pitch, voxels (radii above 1)
+    StagedUnits<int2> units;            // radii above 1: built here; radius 1: built on the device
     int64_t nunits = 0;           // unit entries of the workspace (radius 1: the most the device may append)
 };
 
@@ -646,35 +659,30 @@ dare_status run_batch(const dare_volume* const* vols, const dare_slice_spec* spe
         if (R <= 1) {
             g.nunits += tile_units_max(specs[k].width, specs[k].height);
         } else {
-            const int64_t u = staged_tiles(specs[k].width, specs[k].height);
-            for (int64_t t = 0; t < u; ++t) g.units.push_back(make_int2(r, (int)t));
+            add_staged_units(vols[k], specs + k, r, g.units);
             g.nunits += batch_units(R, specs[k].width, specs[k].height);
-            g.pitch = std::max(g.pitch, pitch_vox(vols[k], specs + k));
         }
         g.reqs.push_back(q);
     }
     for (auto& kv : groups)   // units are indexed in 32 bits on the device
         if (kv.second.nunits >= INT32_MAX) return DARE_ERR_INVALID_ARG;
     std::vector<char> host;
+    std::vector<int2> units;
     for (auto& kv : groups) {
         Group& g = kv.second;
         const int R = std::get<1>(kv.first);
         const bool host_units = R > 1;
         const int nreq = (int)g.reqs.size();
         const GroupLayout L = group_layout(g.reqs.size(), (size_t)g.nunits, host_units);
-        const uint64_t bytes = host_units ? L.o_units + g.units.size() * sizeof(int2) : L.upload;
-        host.assign(bytes, 0);
         BatchHeader hd{};
-        hd.counts[0] = host_units ? (int)g.units.size() : 0;
+        const int grid = host_units ? g.units.finish(hd.counts, units) : kBatchGrid;
         hd.counts[1] = nreq;
-        const int parts = host_units ? staged_parts((int64_t)g.units.size(), g.pitch) : 1;
-        hd.counts[3] = host_units ? parts : 0;
+        const uint64_t bytes = host_units ? L.o_units + units.size() * sizeof(int2) : L.upload;
+        host.assign(bytes, 0);
         memcpy(host.data(), &hd, sizeof(hd));
         memcpy(host.data() + L.o_req, g.reqs.data(), g.reqs.size() * sizeof(BatchReq));
-        if (host_units && !g.units.empty())
-            memcpy(host.data() + L.o_units, g.units.data(), g.units.size() * sizeof(int2));
+        if (host_units) memcpy(host.data() + L.o_units, units.data(), units.size() * sizeof(int2));
         if (!upload(ws, host.data(), bytes)) return DARE_ERR_HIP;
-        const int grid = R <= 1 ? kBatchGrid : (int)std::min<int64_t>((int64_t)g.units.size() * parts, 65535);
         HIP_TRY(launch_reslice_batch(std::get<0>(kv.first), R, (const BatchReq*)(ws + L.o_req),
                                      (SliceRec*)(ws + L.o_rec), (int2*)(ws + L.o_units), (TileRec*)(ws + L.o_tiles),
                                      (int*)ws, nreq, (int)g.nunits, grid, stream));

@@ -582,19 +582,22 @@ __global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs(const Vo
     wide_tile<DT, R, WideLimits<R>::kThreads>(vd, s, unit, b - unit * parts, parts, L);
 }
 
-// Batched form: (request, tile) units times parts, grid-stride; every tile computes its own setup,
-// so a request's result is the one it gets alone.
+// Batched form, grid-stride: the first counts[2] of the (request, tile) units take counts[3]
+// workgroups each, the others one.  Every tile computes its own setup, so a request's result is
+// the one it gets alone.
 template <int DT, int R>
 __global__ void __launch_bounds__(WideLimits<R>::kThreads) k_reslice_rs_batch(const BatchReq* __restrict__ reqs,
                                                                               const int2* __restrict__ units,
                                                                               const int* __restrict__ counts) {
     __shared__ WideLds<DT, R> L;
-    const int parts = max(counts[3], 1);
-    const int64_t n = (int64_t)counts[0] * parts;
-    for (int64_t b = blockIdx.x; b < n; b += gridDim.x) {
-        const int u = (int)(b / parts), part = (int)(b - (int64_t)u * parts);
+    // coarse units times parts is a few workgroups per CU more than the units at most: 32 bits
+    const uint32_t parts = (uint32_t)max(counts[3], 1), coarse = (uint32_t)counts[2] * parts;
+    const uint32_t n = coarse + (uint32_t)(counts[0] - counts[2]);
+    for (uint32_t b = blockIdx.x; b < n; b += gridDim.x) {
+        const bool c = b < coarse;
+        const uint32_t u = c ? b / parts : b - coarse + (uint32_t)counts[2], part = c ? b - u * parts : 0;
         const int r = ui(units[u].x), t = ui(units[u].y);
-        wide_tile<DT, R, WideLimits<R>::kThreads>(reqs[r].vol, reqs[r].s, t, part, parts, L);
+        wide_tile<DT, R, WideLimits<R>::kThreads>(reqs[r].vol, reqs[r].s, t, (int)part, c ? (int)parts : 1, L);
         __syncthreads();
     }
 }
@@ -634,21 +637,14 @@ static hipError_t launch_many(int radius, const BatchReq* reqs, const int2* unit
     return hipGetLastError();
 }
 
-// Workgroups per 16 x 16 tile.  Where the output is too coarse for a tile to stage in one piece (its
-// extent beyond about 10 voxels), its pieces are spread over workgroups, up to 64 workgroups per CU
-// in all: few tiles of a coarse view meet the grid, and those hold most of its work.  512 x 512
-// pixels 16 voxels apart at R = 2, 6, 8: 287, 467, 727 us per slice with 8 workgroups per CU, 87, 163,
-// 245 us with 64.
-int staged_parts(int64_t tiles, double pitch_vox) {
-    int edge = kTile;
-    while (edge > 1 && (double)(edge - 1) * pitch_vox > 10.0) edge >>= 1;
-    const int64_t pieces = (int64_t)(kTile / edge) * (kTile / edge);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(pieces, 16384 / std::max<int64_t>(tiles, 1)));
-}
-
+// A single request whose output is too coarse for a tile to stage in one piece (its extent beyond
+// about 10 voxels) has its tiles' pieces spread over workgroups, up to 64 workgroups per CU in all:
+// few tiles of a coarse view meet the grid, and those hold most of its work.  512 x 512 pixels 16
+// voxels apart at R = 2, 6, 8: 287, 467, 727 us per slice with 8 workgroups per CU, 87, 163, 245 us
+// with 64.
 hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, double pitch_vox,
                                  hipStream_t stream) {
-    const int parts = staged_parts(staged_tiles(s.W, s.H), pitch_vox);
+    const int parts = tile_parts(staged_tiles(s.W, s.H), tile_pieces(pitch_vox));
 #define L(D) return launch_one<D>(vd, radius, s, parts, stream)
     DARE_DISPATCH_DT(dtype, L)
 #undef L

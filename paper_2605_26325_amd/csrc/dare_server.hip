@@ -38,7 +38,7 @@ namespace dare {
 const VolDev* volume_device(const dare_volume* v);
 int volume_dtype(const dare_volume* v);
 int volume_radius(const dare_volume* v);
-double volume_spacing(const dare_volume* v);
+void add_staged_units(const dare_volume* v, const dare_slice_spec* s, int r, StagedUnits<int2>& u);
 int volume_device_id(const dare_volume* v);
 uint64_t volume_arena_size(const dare_volume* v);
 dare_status check_slice_spec(const dare_slice_spec* s);
@@ -330,8 +330,8 @@ bool launch_tick(dare_server* S, Slot& sl) {
     int nreq = 0;
     const bool host_units = S->radius > 1;
     std::vector<BatchReq> breqs;
+    StagedUnits<int2> staged;
     std::vector<int2> bunits;
-    double pitch = 0.0;            // largest output pitch, voxels
     while (!S->queue.empty() && nreq < S->cfg.max_tick_requests) {
         Request& r = S->reqs[S->queue.front()];
         if (r.frames_job) break;               // later requests must see the frames: wait for them
@@ -353,10 +353,7 @@ bool launch_tick(dare_server* S, Slot& sl) {
         q.s.tiles = q.s.tiles_x * ((r.spec.height + kTile - 1) / kTile);
         q.s.out = (float*)(S->arena + off);
         breqs.push_back(q);
-        if (host_units)
-            for (int64_t t = 0, nt = staged_tiles(r.spec.width, r.spec.height); t < nt; ++t)
-                bunits.push_back(make_int2(nreq, (int)t));
-        pitch = std::max(pitch, std::max(q.s.sx, q.s.sy) / volume_spacing(S->vols[r.vol].v));
+        if (host_units) add_staged_units(S->vols[r.vol].v, &r.spec, nreq, staged);
         sl.tickets.push_back(S->queue.front());
         S->queue.pop_front();
         pixels += px;
@@ -366,9 +363,8 @@ bool launch_tick(dare_server* S, Slot& sl) {
     if (nreq == 0) return false;
     choose_direct(S, breqs, sl.tickets);
     BatchHeader hd{};
-    hd.counts[0] = host_units ? (int)bunits.size() : 0;   // radius 1: the setup pass appends the units
+    if (host_units) staged.finish(hd.counts, bunits);   // radius 1: the setup pass appends the units
     hd.counts[1] = nreq;
-    hd.counts[3] = host_units ? staged_parts((int64_t)bunits.size(), pitch) : 0;
     memcpy(sl.staging, &hd, sizeof(hd));
     memcpy(sl.staging + S->o_req, breqs.data(), breqs.size() * sizeof(BatchReq));
     if (host_units) memcpy(sl.staging + S->o_units, bunits.data(), bunits.size() * sizeof(int2));

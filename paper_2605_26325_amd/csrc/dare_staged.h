@@ -3,15 +3,14 @@
 #pragma once
 
 #include "dare_batch.h"
+#include "dare_pieces.h"
 
 namespace dare {
 
 // `pitch_vox`: the larger output pitch in voxels.
 hipError_t launch_reslice_staged(const VolDev* vd, int dtype, int radius, const SliceArgs& s, double pitch_vox,
                                  hipStream_t stream);
-// Batched form over (request, tile) units; counts[0] holds the number of units and counts[3] the
-// workgroups per unit (staged_parts).
-int staged_parts(int64_t tiles, double pitch_vox);
+// Batched form: counts[0] units, the first counts[2] of them with counts[3] workgroups each.
 hipError_t launch_reslice_staged_batch(int dtype, int radius, const BatchReq* reqs, const int2* units,
                                        const int* counts, int grid, hipStream_t stream);
 // Work units of a W x H request: its 16 x 16 tiles.
