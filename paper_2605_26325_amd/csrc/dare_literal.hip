@@ -27,6 +27,7 @@
 
 #include "dare_frames.h"
 #include "dare_host.h"
+#include "dare_sample_tiles.h"
 
 #pragma clang fp contract(off)
 
@@ -36,7 +37,6 @@ namespace {
 
 constexpr int kScanBlock = 1024;          // counts scanned per workgroup (4 per thread)
 constexpr int kLutLds = 8192;             // frames whose weights a reslice workgroup keeps in LDS
-constexpr int kTileBox = 1536;            // voxels whose sums a tiled reslice workgroup keeps in LDS
 constexpr int32_t kMaxFrames = 1 << 24;   // frame index bits of a packed sample
 constexpr uint64_t kAlignBytes = 256;
 
@@ -327,7 +327,7 @@ __device__ inline float blend_range(const LitSlice& s, const double c[3], const 
 // one thread, into LDS; every pixel then blends from LDS in the same voxel order as above, so
 // the result is the same as summing per pixel.  A tile whose box exceeds kTileBox voxels (coarse
 // output pitch, large radius) does sum per pixel; the launch takes tiles of 8 or 4 pixels square
-// where 16 would (`tile_shift`): all the threads then sum the voxels, and a part of them has pixels.
+// where 16 would (`sample_tile_shift`): all the threads then sum the voxels, and a part of them has pixels.
 // CUBE: the box reading at R = 1, where a pixel inside the grid takes a whole 3 x 3 x 3 cube (its reads
 // unrolled: 23.3 -> 20.7 us for a 512 x 512 slice; in one kernel with the other readings they made
 // those 2 % slower).
@@ -439,22 +439,6 @@ __global__ void __launch_bounds__(256) k_lit_reslice_tiled(SampleDev d, LitSlice
                             sw = q.x;
                             swi = q.y;
                         });
-}
-
-// log2 of the tile edge of a launch: the largest of 16, 8 and 4 pixels whose box of voxels (its extent
-// and the reading's reach) has at most kTileBox wherever it falls; 16 where none has.  Two 489 x
-// 137 slices at R = 2, 0.6 voxels per pixel, box reading: 599 us with 16 x 16 tiles that sum per pixel,
-// 69 us with 8 x 8 tiles; 300 x 300 at R = 1, 0.8 voxels 180 and 37 us.
-int tile_shift(const LitSlice& s, double inv_h) {
-    for (int shift = 4; shift >= 2; --shift) {
-        double box = 1.0;
-        for (int a = 0; a < 3; ++a) {
-            const double step = (fabs(s.sx * s.e0[a]) + fabs(s.sy * s.e1[a])) * inv_h;
-            box *= floor(((1 << shift) - 1) * step + 1e-6) + 2.0 * s.R + 2.0;
-        }
-        if (box <= (double)kTileBox) return shift;
-    }
-    return 4;
 }
 
 // Empty store: every voxel's range is [0, 0).
@@ -658,9 +642,11 @@ dare_status dare_samples_reslice(const dare_samples* st, const dare_params* p, c
         hipLaunchKernelGGL(k_lit_lut, dim3((st->d.n_frames + 255) / 256), dim3(256), 0, stream, st->d, la);
     }
     const size_t lds = st->d.n_frames <= kLutLds ? (size_t)st->d.n_frames * sizeof(float) : 0;
-    const int shift = tile_shift(s, 1.0 / st->g.spacing_mm), edge = 1 << shift;
-    const int tiles_x = (s.W + edge - 1) >> shift;
-    const int64_t tiles = (int64_t)tiles_x * ((s.H + edge - 1) >> shift);
+    const double inv_h = 1.0 / st->g.spacing_mm;
+    double step[3];
+    for (int a = 0; a < 3; ++a) step[a] = (fabs(s.sx * s.e0[a]) + fabs(s.sy * s.e1[a])) * inv_h;
+    const int shift = sample_tile_shift(step, s.R, s.W, s.H), tiles_x = (s.W + (1 << shift) - 1) >> shift;
+    const int64_t tiles = sample_tiles(s.W, s.H, shift);
     hipLaunchKernelGGL(s.mode == DARE_LITERAL_BOX && s.R == 1 ? k_lit_reslice_tiled<true> : k_lit_reslice_tiled<false>,
                        dim3((unsigned)tiles), dim3(256), lds, stream, st->d, s, tiles_x, shift);
     return hip_status(hipGetLastError());
