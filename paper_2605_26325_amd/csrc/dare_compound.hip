@@ -11,6 +11,7 @@
 #include "dare_codec.h"
 #include "dare_frames.h"
 #include "dare_internal.h"
+#include "dare_patches.h"
 
 #pragma clang fp contract(off)
 
@@ -82,24 +83,22 @@ __device__ __forceinline__ int64_t brick_entry(const VolDev* vd, int b, int vx, 
     return (int64_t)b * vd->nbricks + ((int64_t)(vz >> 3) * vd->nby + (vy >> 3)) * vd->nbx + (vx >> 3);
 }
 
-// The per-pixel passes take 32 x 32 pixel patches, one per workgroup, four pixels per thread.  A
-// wave's 64 lanes are an 8 x 8 block of the image at a time (four such blocks side by side), not
-// 64 pixels of a row: the block falls on 8 x 8 neighbouring voxels of a brick or four, whose
-// accumulators lie in whole 64-byte cubes of 2 x 2 x 2, where a row of 64 touches 32 cubes in 9
-// bricks.
-constexpr int kPatch = 32;
+// The per-pixel passes take patches of 1024 pixels (dare_patches.h), one per workgroup, four pixels
+// per thread.  A wave's 64 lanes are an 8 x 8 block of the image at a time, not 64 pixels of a row:
+// the block falls on 8 x 8 neighbouring voxels of a brick or four, whose accumulators lie in whole
+// 64-byte cubes of 2 x 2 x 2, where a row of 64 touches 32 cubes in 9 bricks.
 
-// Patch (first column and row) and frame of this workgroup in a flat grid of nx x ny patches per
+// Patch (column and row) and frame of this workgroup in a flat grid of the patches of every
 // frame.  Workgroups are dealt to the 8 XCDs round-robin; when a frame's patches are a multiple of
 // 8, XCD x takes the x-th eighth of every frame's patches (a band of image rows).  Frames of a
 // sweep are near-parallel, so a band of rows falls on the same part of the volume frame after
 // frame, and each XCD's L2 keeps the accumulators of its own part instead of all eight sharing
 // every line.  The launch covers frames f0, f0 + 1, ...
 struct Patch {
-    int i, j, f;
+    int x, y, f;
 };
-__device__ __forceinline__ Patch frame_patch(int nx, int ny, int f0) {
-    const int g = blockIdx.x, np = nx * ny;
+__device__ __forceinline__ Patch frame_patch(const PatchShape& s, int f0) {
+    const int g = blockIdx.x, np = s.nx * s.ny;
     int f, p;
     if ((np & 7) == 0) {
         const int per = np >> 3, k = g >> 3;
@@ -109,15 +108,13 @@ __device__ __forceinline__ Patch frame_patch(int nx, int ny, int f0) {
         f = g / np;
         p = g - f * np;
     }
-    const int y = p / nx;
-    return Patch{(p - y * nx) * kPatch, y * kPatch, f0 + f};
+    const int y = p / s.nx;
+    return Patch{p - y * s.nx, y, f0 + f};
 }
 
 // Pixel b (0..3) of this thread in its patch.
-__device__ __forceinline__ void patch_pixel(const Patch& p, int b, int& i, int& j) {
-    const int lane = threadIdx.x & 63;
-    i = p.i + b * 8 + (lane & 7);
-    j = p.j + (int)(threadIdx.x >> 6) * 8 + (lane >> 3);
+__device__ __forceinline__ PatchPixel patch_pixel(const PatchShape& s, const Patch& p, int b) {
+    return patch_pixel(s, p.x, p.y, (int)(threadIdx.x >> 6) * 4 + b, (int)threadIdx.x & 63);
 }
 
 // The (bin, brick) entry and the place in the brick of the four pixels of this thread: entry -1
@@ -319,20 +316,20 @@ __device__ __forceinline__ void mark_one(VolDev* vd, int64_t e) {
 // with its own addition, took 1190 us; 30 frames of 512^2 into resident bricks 254 -> 71 us.
 constexpr int kMarkSet = 256;
 template <bool FAN>
-__device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, double sx, double sy, const FanArgs* fan, int f0) {
+__device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, const PatchShape& shape, double sx, double sy, const FanArgs* fan, int f0) {
     __shared__ int set[kMarkSet];
     __shared__ uint32_t count[2], first[2];   // the workgroup's new entries and dirty slots
     if (threadIdx.x < 2) count[threadIdx.x] = 0u;
     for (int k = threadIdx.x; k < kMarkSet; k += 256) set[k] = -1;
-    const Patch p = frame_patch((w + kPatch - 1) / kPatch, (h + kPatch - 1) / kPatch, f0);
+    const Patch p = frame_patch(shape, f0);
     const FramePixels<FAN> px(vd, fan, p.f, w);
     __syncthreads();
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        int i, j, local;
-        patch_pixel(p, b, i, j);
-        const int e = (int)px.entry(i, j, h, sx, sy, local);   // entries fit the lists' 32 bits
+        int local;
+        const PatchPixel at = patch_pixel(shape, p, b);
+        const int e = (int)px.entry(at.i, at.j, h, sx, sy, local);   // entries fit the lists' 32 bits
         const int left = __shfl_up(e, 1), up = __shfl_up(e, 8);
         bool mine = e >= 0 && !(lane >= 1 && left == e) && !(lane >= 8 && up == e);
         if (mine) {
@@ -366,8 +363,9 @@ __device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, double sx, 
     if (m == kDirty) append_dirty(vd, first[1] + at_d, slot);
 }
 
-__global__ void __launch_bounds__(256) k_mark_pixels(VolDev* vd, int w, int h, double sx, double sy, int f0) {
-    mark_patch<false>(vd, w, h, sx, sy, nullptr, f0);
+__global__ void __launch_bounds__(256) k_mark_pixels(VolDev* vd, int w, int h, PatchShape shape, double sx, double sy,
+                                                     int f0) {
+    mark_patch<false>(vd, w, h, shape, sx, sy, nullptr, f0);
 }
 
 // Fan probes: one frame descriptor per (frame, sector), each with the frame's pose and the
@@ -383,8 +381,8 @@ __global__ void k_compose_fan(VolDev* vd, const float* __restrict__ poses, int n
 }
 
 // K3a for fan frames.
-__global__ void __launch_bounds__(256) k_mark_fan(VolDev* vd, int w, int h, FanArgs fan, int f0) {
-    mark_patch<true>(vd, w, h, 0.0, 0.0, &fan, f0);
+__global__ void __launch_bounds__(256) k_mark_fan(VolDev* vd, int w, int h, PatchShape shape, FanArgs fan, int f0) {
+    mark_patch<true>(vd, w, h, shape, 0.0, 0.0, &fan, f0);
 }
 
 // Undo the marks of a rejected batch and restore the codebook size.
@@ -462,8 +460,9 @@ __device__ __forceinline__ void merge_pixels(int& place, int local, uint32_t& ad
 // voxel first takes 300 fan frames (about 6 pixels a voxel) from 523 to 188 us.
 template <bool FAN>
 __device__ __forceinline__ void accumulate_patch(const VolDev* __restrict__ vd, const uint8_t* __restrict__ frames,
-                                                 int w, int h, double sx, double sy, const FanArgs* fan, int f0) {
-    const Patch p = frame_patch((w + kPatch - 1) / kPatch, (h + kPatch - 1) / kPatch, f0);
+                                                 int w, int h, const PatchShape& shape, double sx, double sy,
+                                                 const FanArgs* fan, int f0) {
+    const Patch p = frame_patch(shape, f0);
     const FramePixels<FAN> px(vd, fan, p.f, w);
     const gptr<unsigned long long> acc = (gptr<unsigned long long>)((cptr<VolDev>)vd)->acc;
     const gptr<const uint8_t> img = (gptr<const uint8_t>)frames + (size_t)p.f * w * h;
@@ -474,10 +473,9 @@ __device__ __forceinline__ void accumulate_patch(const VolDev* __restrict__ vd, 
     uint32_t inten[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        int i, j;
-        patch_pixel(p, b, i, j);
-        e[b] = px.entry(i, j, h, sx, sy, local[b]);
-        inten[b] = img[e[b] >= 0 ? (size_t)j * w + i : 0];
+        const PatchPixel at = patch_pixel(shape, p, b);
+        e[b] = px.entry(at.i, at.j, h, sx, sy, local[b]);
+        inten[b] = img[e[b] >= 0 ? (size_t)at.j * w + at.i : 0];
         slot[b] = ((gptr<const int32_t>)px.v.table)[e[b] >= 0 ? e[b] : 0];
     }
 #pragma unroll
@@ -494,15 +492,15 @@ __device__ __forceinline__ void accumulate_patch(const VolDev* __restrict__ vd, 
 }
 
 __global__ void __launch_bounds__(256) k_accumulate(const VolDev* __restrict__ vd, const uint8_t* __restrict__ frames,
-                                                    int w, int h, double sx, double sy, int f0) {
-    accumulate_patch<false>(vd, frames, w, h, sx, sy, nullptr, f0);
+                                                    int w, int h, PatchShape shape, double sx, double sy, int f0) {
+    accumulate_patch<false>(vd, frames, w, h, shape, sx, sy, nullptr, f0);
 }
 
 // K4 for fan frames.
 __global__ void __launch_bounds__(256) k_accumulate_fan(const VolDev* __restrict__ vd,
-                                                        const uint8_t* __restrict__ frames, int w, int h, FanArgs fan,
-                                                        int f0) {
-    accumulate_patch<true>(vd, frames, w, h, 0.0, 0.0, &fan, f0);
+                                                        const uint8_t* __restrict__ frames, int w, int h,
+                                                        PatchShape shape, FanArgs fan, int f0) {
+    accumulate_patch<true>(vd, frames, w, h, shape, 0.0, 0.0, &fan, f0);
 }
 
 // K5: exact sums -> stored (value, count) pairs of every dirty slot.
@@ -708,17 +706,6 @@ static inline int grid_for(int64_t n, int block, int cap = 65536) {
     return (int)(g > cap ? cap : g);
 }
 
-static int64_t frame_patches(int w, int h) {
-    return (int64_t)((w + kPatch - 1) / kPatch) * ((h + kPatch - 1) / kPatch);
-}
-
-// Frames per launch of the per-pixel passes (flat grids of patches x frames), so that a grid stays
-// below 2^24 workgroups.
-int frames_per_launch(int n, int w, int h) {
-    const int64_t fc = ((int64_t)1 << 24) / frame_patches(w, h);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(n, fc));
-}
-
 hipError_t launch_compose_frames(const VolDev* vd, const float* poses, int n, hipStream_t stream) {
     hipLaunchKernelGGL(k_compose_frames, dim3((n + 63) / 64), dim3(64), 0, stream, const_cast<VolDev*>(vd), poses, n);
     return hipGetLastError();
@@ -730,10 +717,11 @@ hipError_t launch_assign_bins(VolDev* vd, int n, int K0, hipStream_t stream) {
 }
 
 hipError_t launch_mark_pixels(const VolDev* vd, int n, int w, int h, double sx, double sy, hipStream_t stream) {
-    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
+    const PatchShape shape = patch_shape(w, h);
+    const int np = shape.nx * shape.ny, fc = frames_per_launch(n, shape);
     for (int f0 = 0; f0 < n; f0 += fc)
         hipLaunchKernelGGL(k_mark_pixels, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream,
-                           const_cast<VolDev*>(vd), w, h, sx, sy, f0);
+                           const_cast<VolDev*>(vd), w, h, shape, sx, sy, f0);
     return hipGetLastError();
 }
 
@@ -746,19 +734,21 @@ hipError_t launch_compose_fan(const VolDev* vd, const float* poses, int n, const
 }
 
 hipError_t launch_mark_fan(const VolDev* vd, int n, int w, int h, const FanArgs& fan, hipStream_t stream) {
-    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
+    const PatchShape shape = patch_shape(w, h);
+    const int np = shape.nx * shape.ny, fc = frames_per_launch(n, shape);
     for (int f0 = 0; f0 < n; f0 += fc)
         hipLaunchKernelGGL(k_mark_fan, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream,
-                           const_cast<VolDev*>(vd), w, h, fan, f0);
+                           const_cast<VolDev*>(vd), w, h, shape, fan, f0);
     return hipGetLastError();
 }
 
 hipError_t launch_accumulate_fan(const VolDev* vd, const uint8_t* frames, int n, int w, int h, const FanArgs& fan,
                                  hipStream_t stream) {
-    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
+    const PatchShape shape = patch_shape(w, h);
+    const int np = shape.nx * shape.ny, fc = frames_per_launch(n, shape);
     for (int f0 = 0; f0 < n; f0 += fc)
         hipLaunchKernelGGL(k_accumulate_fan, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h,
-                           fan, f0);
+                           shape, fan, f0);
     return hipGetLastError();
 }
 
@@ -778,10 +768,11 @@ hipError_t launch_alloc(VolDev* vd, uint32_t new_count, uint32_t used, uint32_t 
 
 hipError_t launch_accumulate(const VolDev* vd, const uint8_t* frames, int n, int w, int h, double sx, double sy,
                              hipStream_t stream) {
-    const int np = (int)frame_patches(w, h), fc = frames_per_launch(n, w, h);
+    const PatchShape shape = patch_shape(w, h);
+    const int np = shape.nx * shape.ny, fc = frames_per_launch(n, shape);
     for (int f0 = 0; f0 < n; f0 += fc)
-        hipLaunchKernelGGL(k_accumulate, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h, sx,
-                           sy, f0);
+        hipLaunchKernelGGL(k_accumulate, dim3(np * std::min(fc, n - f0)), dim3(256), 0, stream, vd, frames, w, h,
+                           shape, sx, sy, f0);
     return hipGetLastError();
 }
 
