@@ -136,8 +136,10 @@ dare_status dare_volume_destroy(dare_volume* v);
  * Synchronises `stream` once per batch of up to 4096 frames (pose check and
  * budget admission); the final finalize step is left enqueued.
  * Errors: INVALID_ARG, BAD_POSE (a frame pose is not rigid: that batch is
- * rolled back), BUDGET (the new bricks do not fit: that batch is rolled
- * back), HIP.  Returns DARE_WARN_BINS_SATURATED when the codebook is full. */
+ * rolled back), BUDGET (the new bricks do not fit, or a pixel lies in entry
+ * bin * bricks per bin + brick >= 2^31 of the brick table, which only grids of
+ * more than 2^31 / max_bins bricks have: that batch is rolled back), HIP.
+ * Returns DARE_WARN_BINS_SATURATED when the codebook is full. */
 dare_status dare_reconstruct_frames(dare_volume* v, const uint8_t* frames_dev, int32_t n, int32_t w,
                                     int32_t h, const double pitch_mm[2], const float* probe_poses_dev,
                                     void* stream);

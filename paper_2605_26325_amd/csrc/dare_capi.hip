@@ -536,7 +536,7 @@ dare_status reconstruct_batches(dare_volume* v, const uint8_t* frames_dev, int32
                 retried = true;
                 continue;
             }
-            return bad ? DARE_ERR_BAD_POSE : DARE_ERR_BUDGET;
+            return (st.bad_pose & kBadPose) ? DARE_ERR_BAD_POSE : DARE_ERR_BUDGET;
         }
         HIP_TRY(launch_alloc(vd, st.new_count, used, st.dirty_count, stream));
         const uint8_t* fr = frames_dev + (size_t)f0 * w * h;
@@ -1033,7 +1033,7 @@ dare_status dare_volume_upload_sums(dare_volume* v, const double* rep_n, const d
     VolState st;
     dare_status s = read_state(v, stream, &st);
     if (s != DARE_OK) return s;
-    if (st.new_count > h.cap) {
+    if (st.new_count > h.cap || st.bad_pose) {
         HIP_TRY(launch_rollback(v->dev, st.new_count, 0, 0, 0, stream));
         HIP_TRY(launch_clear_marks(h.table, (int64_t)v->p.max_bins * h.nbricks, stream));
         HIP_TRY(hipStreamSynchronize(stream));

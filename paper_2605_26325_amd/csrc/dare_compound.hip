@@ -158,7 +158,7 @@ __global__ void k_compose_frames(VolDev* vd, const float* __restrict__ poses, in
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     if (f >= n) return;
     FrameDesc d;
-    if (!compose_frame(poses + (size_t)f * 16, vd->calib, vd->normal_axis, d)) atomicOr(&vd->st.bad_pose, 1);
+    if (!compose_frame(poses + (size_t)f * 16, vd->calib, vd->normal_axis, d)) atomicOr(&vd->st.bad_pose, kBadPose);
     vd->frames[f] = d;
 }
 
@@ -300,6 +300,10 @@ __device__ __forceinline__ void append_dirty(VolDev* vd, uint32_t k, int slot) {
 }
 __device__ __forceinline__ void mark_one(VolDev* vd, int64_t e) {
     int slot;
+    if (e > INT32_MAX) {
+        atomicOr(&vd->st.bad_pose, kBadEntry);
+        return;
+    }
     const Marked m = mark_entry(vd, e, slot);
     if (m == kNew) append_new(vd, atomicAdd(&vd->st.new_count, 1u), e);
     if (m == kDirty) append_dirty(vd, atomicAdd(&vd->st.dirty_count, 1u), slot);
@@ -325,11 +329,14 @@ __device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, const Patch
     const FramePixels<FAN> px(vd, fan, p.f, w);
     __syncthreads();
     const int lane = threadIdx.x & 63;
+    bool past = false;            // a pixel in an entry that the lists' 32 bits do not hold
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         int local;
         const PatchPixel at = patch_pixel(shape, p, b);
-        const int e = (int)px.entry(at.i, at.j, h, sx, sy, local);   // entries fit the lists' 32 bits
+        const int64_t entry = px.entry(at.i, at.j, h, sx, sy, local);
+        past = past || entry > INT32_MAX;
+        const int e = (uint64_t)entry > (uint64_t)INT32_MAX ? -1 : (int)entry;
         const int left = __shfl_up(e, 1), up = __shfl_up(e, 8);
         bool mine = e >= 0 && !(lane >= 1 && left == e) && !(lane >= 8 && up == e);
         if (mine) {
@@ -342,6 +349,7 @@ __device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, const Patch
             if (mine) mark_one(vd, e);   // no free place for it
         }
     }
+    if (__ballot(past) && lane == 0) atomicOr(&vd->st.bad_pose, kBadEntry);
     __syncthreads();
     const int e = set[threadIdx.x];
     int slot = -1;
@@ -375,7 +383,7 @@ __global__ void k_compose_fan(VolDev* vd, const float* __restrict__ poses, int n
     if (k >= n * fan.sectors) return;
     const int f = k / fan.sectors;
     FrameDesc d;
-    if (!compose_frame(poses + (size_t)f * 16, vd->calib, 2, d)) atomicOr(&vd->st.bad_pose, 1);
+    if (!compose_frame(poses + (size_t)f * 16, vd->calib, 2, d)) atomicOr(&vd->st.bad_pose, kBadPose);
     fan_sector_axis(d, fan, width, k - f * fan.sectors);
     vd->frames[k] = d;
 }

@@ -39,10 +39,14 @@ constexpr int kMaxBins = 64;
 constexpr int kFrameChunk = 4096;
 constexpr int kTile = 16;                 // reslice output tile edge (pixels)
 
+// Why a batch of frames cannot be taken: a pose that is not rigid; a pixel in a table entry past what
+// the 32-bit lists of new entries hold (bins x bricks per bin beyond 2^31).
+constexpr int kBadPose = 1, kBadEntry = 2;
+
 struct VolState {                         // read back by the host at sync points
     int32_t K;
     int32_t saturated;
-    int32_t bad_pose;
+    int32_t bad_pose;                     // kBadPose, kBadEntry
     uint32_t used;                        // allocated slots
     uint32_t new_count;                   // entries marked by the current batch
     uint32_t dirty_count;                 // slots to finalize
