@@ -637,36 +637,43 @@ __global__ void k_dense_scatter(const VolDev* vd, const uint32_t* __restrict__ S
 }
 
 // Every voxel's exact sum and count as dense arrays.  A wave takes a row of 8 bricks along x (64
-// voxels) and stores it row by row, so that the waves of a workgroup, at consecutive rows of bricks,
-// fill long runs in order; its loads go cube by cube, so each line of a brick is read once.  Bound by
-// the bytes (3.5 GB written and 2 GB read for 26 bins of 256^3): 1150 us, 4.8 TB/s; a thread per
-// voxel index, with its 64-bit divisions, took 2610 us, and rows of 8 bricks stored 64 rows apart
-// (8 waves' worth of scattered 256-byte pieces) 3930 us.
+// voxels; 4, 2 or 1 bricks where the grid is that narrow, and as many more rows of y at a time) and
+// stores it row by row, so that the waves of a workgroup, at consecutive rows of bricks, fill long
+// runs in order; its loads go cube by cube, so each line of a brick is read once.  Bound by the bytes
+// (3.5 GB written and 2 GB read for 26 bins of 256^3): 1150 us, 4.8 TB/s; a thread per voxel index,
+// with its 64-bit divisions, took 2610 us, and rows of 8 bricks stored 64 rows apart (8 waves' worth
+// of scattered 256-byte pieces) 3930 us.  6 bins of 8 x 256 x 256, the whole call: 29 us, 51 in rows
+// of 64, 39 by voxel index.
+template <int LW>                           // log2 of the voxels along x
 __global__ void __launch_bounds__(256) k_download_sums(const VolDev* __restrict__ vd, uint32_t* __restrict__ S,
-                                                       uint32_t* __restrict__ C, int b0, int64_t items) {
-    int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // (bin, bz, by, row of bricks)
+                                                       uint32_t* __restrict__ C, int64_t first, int64_t items) {
+    constexpr int kRows = 64 >> LW, kSteps = 8 / kRows;             // rows of y at a time, and how often
+    constexpr int kLoads = LW == 6 ? 16 : 8, kZ = kLoads / kSteps;   // in flight at a time
+    int64_t g = first + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // (bin, bz, by, row of bricks)
     if (g >= items) return;
-    const int nxr = (vd->nbx + 7) / 8, nx = vd->nx, ny = vd->ny, nz = vd->nz;
+    const int nx = vd->nx, ny = vd->ny, nz = vd->nz, nxr = (nx + (1 << LW) - 1) >> LW;
     const int lane = threadIdx.x & 63;
-    const int vx = (int)(g % nxr) * 64 + lane;
+    const int vx = (int)(g % nxr) * (1 << LW) + (lane & ((1 << LW) - 1)), dy = lane >> LW;
     g /= nxr;
     const int y0 = (int)(g % vd->nby) * 8;
     g /= vd->nby;
     const int z0 = (int)(g % vd->nbz) * 8, bin = (int)(g / vd->nbz);
     const bool in = vx < nx;
-    const int slot = in ? vd->table[brick_entry(vd, b0 + bin, vx, y0, z0)] : -1;
+    const int slot = in ? vd->table[brick_entry(vd, bin, vx, y0, z0)] : -1;
     const gptr<const unsigned long long> acc = (gptr<const unsigned long long>)vd->acc + (size_t)max(slot, 0) * kBrickVox;
-    for (int z = 0; z < 8; z += 2) {
-        unsigned long long u[16];
+#pragma unroll 1
+    for (int z = 0; z < 8; z += kZ) {
+        unsigned long long u[kLoads];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
+        for (int k = 0; k < kLoads; ++k) {
             u[k] = 0ull;
-            if (slot >= 0) u[k] = acc[brick_local(vx, k >> 1, z + (k & 1))];
+            if (slot >= 0) u[k] = acc[brick_local(vx, k / kZ * kRows + dy, z + k % kZ)];
         }
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int vz = z0 + z + (k >> 3), vy = y0 + (k & 7);
-            const unsigned long long x = u[((k & 7) << 1) | (k >> 3)];
+        for (int k = 0; k < kLoads; ++k) {
+            const int step = k % kSteps, dz = k / kSteps;
+            const int vz = z0 + z + dz, vy = y0 + step * kRows + dy;
+            const unsigned long long x = u[step * kZ + dz];
             if (!in || vy >= ny || vz >= nz) continue;
             const size_t at = (((size_t)bin * nz + vz) * ny + vy) * nx + vx;
             // written once, read by no kernel here: past the caches
@@ -820,12 +827,13 @@ hipError_t launch_dense_scatter(const VolDev* vd, const uint32_t* S, const uint3
 
 hipError_t launch_download_sums(const VolDev* vd, uint32_t* S, uint32_t* C, int K, int nx, int ny, int nz,
                                 hipStream_t stream) {
-    const int64_t rows = (int64_t)((nx + 63) / 64) * ((ny + 7) / 8) * ((nz + 7) / 8);
-    const int per = (int)std::max<int64_t>(1, ((int64_t)1 << 23) / rows);   // bins per launch
-    const size_t nvox = (size_t)nx * ny * nz;
-    for (int b0 = 0; b0 < K; b0 += per)
-        hipLaunchKernelGGL(k_download_sums, dim3((unsigned)((rows * std::min(per, K - b0) + 3) / 4)), dim3(256), 0,
-                           stream, vd, S + b0 * nvox, C + b0 * nvox, b0, rows * std::min(per, K - b0));
+    const int lw = nx <= 8 ? 3 : nx <= 16 ? 4 : nx <= 32 ? 5 : 6;
+    const int64_t rows = (int64_t)((nx + (1 << lw) - 1) >> lw) * ((ny + 7) / 8) * ((nz + 7) / 8), items = rows * K;
+    auto* const kernel = lw == 3 ? k_download_sums<3> : lw == 4 ? k_download_sums<4> : lw == 5 ? k_download_sums<5> : k_download_sums<6>;
+    const int64_t most = (int64_t)1 << 25;   // waves per launch: a launch takes at most 2^32 - 1 threads
+    for (int64_t first = 0; first < items; first += most)
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((std::min(most, items - first) + 3) / 4)), dim3(256), 0, stream, vd, S, C,
+                           first, std::min(items, first + most));
     return hipGetLastError();
 }
 
