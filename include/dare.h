@@ -389,8 +389,10 @@ dare_status dare_samples_reslice(const dare_samples* s, const dare_params* p, co
  *   workspace_dev / workspace_bytes: device scratch, at least
  *              dare_compare_workspace_bytes(), 8-byte aligned
  *   out_host   4 doubles: NCC, mean SSIM (NaN when undefined), pixels used
- *              for NCC, windows used for SSIM.
- * Synchronises `stream`.  Errors: INVALID_ARG, HIP. */
+ *              for NCC, windows used for SSIM.  Into pinned memory (of
+ *              hipHostMalloc) the kernels write them directly; any other host
+ *              memory takes a copy command.
+ * Allocates nothing.  Synchronises `stream`.  Errors: INVALID_ARG, HIP. */
 uint64_t dare_compare_workspace_bytes(void);
 dare_status dare_compare_to_frame(const float* image_dev, const uint8_t* frame_dev, int32_t w, int32_t h,
                                   void* workspace_dev, uint64_t workspace_bytes, double* out_host, void* stream);

@@ -150,7 +150,7 @@ def _load():
         "dare_volume_restore_box": (ct.c_int, [V, ct.POINTER(I32), ct.POINTER(I32), P]),
         "dare_volume_set_spill": (ct.c_int, [V, I32]),
         "dare_volume_held": (ct.c_int, [V, ct.POINTER(I64), ct.POINTER(U64)]),
-        "dare_compare_to_frame": (ct.c_int, [P, P, I32, I32, P, U64, ct.POINTER(D), P]),
+        "dare_compare_to_frame": (ct.c_int, [P, P, I32, I32, P, U64, P, P]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(lib, name)
@@ -447,11 +447,12 @@ def compare_to_frame(image, frame, workspace=None, stream=None):
     H, W = image.shape
     if workspace is None:
         workspace = torch.empty(int(lib.dare_compare_workspace_bytes()), dtype=torch.uint8, device=image.device)
-    out = (ct.c_double * 4)()
+    out = torch.empty(4, dtype=torch.float64, pin_memory=True)   # written by the kernels, no copy
     _check(lib.dare_compare_to_frame(_ptr(image.contiguous()), _ptr(frame.contiguous()), int(W), int(H),
-                                     _ptr(workspace), int(workspace.numel()), out, _stream(stream)),
+                                     _ptr(workspace), int(workspace.numel()), out.data_ptr(), _stream(stream)),
            "dare_compare_to_frame", allow_warn=False)
-    return out[0], out[1], int(out[2]), int(out[3])
+    ncc, ssim, pixels, windows = out.tolist()
+    return ncc, ssim, int(pixels), int(windows)
 
 
 LITERAL_MODES = {"box": 0, "tent": 1}

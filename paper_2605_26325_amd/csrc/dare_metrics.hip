@@ -13,8 +13,8 @@
 // finite or outside the image as NaN, which marks every window that holds one), the row sums to
 // LDS in FP64, and each thread sums two pixels of a column and adds its tile's contributions to the
 // eight totals in registers.  Workgroups write their totals to a workspace row each, and one
-// workgroup adds the rows, in a fixed order.  The host finishes NCC from the sums (one pass: FP64
-// keeps the cancellation far below the comparison's tolerance at these sizes).
+// workgroup adds the rows, in a fixed order, and finishes NCC from the sums (one pass: FP64 keeps
+// the cancellation far below the comparison's tolerance at these sizes).
 //
 // Bound: latency, a few dependent phases of two tiles per CU.  512 x 512: 11.0 us and 3.8 us for
 // the total, against 47.8 us and 11.4 us with 121 taps per pixel from global memory and a total of
@@ -23,7 +23,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <mutex>
 
 #include "dare_host.h"
 
@@ -132,9 +131,10 @@ __global__ void __launch_bounds__(256) k_compare(const float* __restrict__ img, 
     if (tid < kSums) partials[(size_t)blockIdx.x * kSums + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
-// The groups' rows added up: thread (row, k) of 32 x 8 takes every 32nd row of total k.
-__global__ void __launch_bounds__(256) k_compare_total(double* __restrict__ partials, int groups,
-                                                       double* __restrict__ host) {
+// The groups' rows added up (thread (row, k) of 32 x 8 takes every 32nd row of total k) and the four
+// results from them, to device memory or to the caller's pinned host memory.
+__global__ void __launch_bounds__(256) k_compare_total(const double* __restrict__ partials, int groups,
+                                                       double* __restrict__ out) {
     __shared__ double red[4][kSums];
     const int k = threadIdx.x % kSums;
     double v = 0.0;
@@ -144,50 +144,32 @@ __global__ void __launch_bounds__(256) k_compare_total(double* __restrict__ part
     for (int off = 32; off >= kSums; off >>= 1) v += __shfl_xor(v, off);
     if ((threadIdx.x & 63) < kSums) red[threadIdx.x >> 6][k] = v;
     __syncthreads();
-    if (threadIdx.x < kSums) (host ? host : partials + (size_t)kMaxGroups * kSums)[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+    if (threadIdx.x != 0) return;
+    double tot[kSums];
+#pragma unroll
+    for (int t = 0; t < kSums; ++t) tot[t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+    const double n = tot[0];
+    double ncc = __builtin_nan("");
+    if (n >= 2.0) {
+        const double saa = tot[3] - tot[1] * tot[1] / n, sbb = tot[4] - tot[2] * tot[2] / n;
+        const double sab = tot[5] - tot[1] * tot[2] / n;
+        if (saa > 0.0 && sbb > 0.0) ncc = sab / sqrt(saa * sbb);
+    }
+    out[0] = ncc;
+    out[1] = tot[7] > 0.0 ? tot[6] / tot[7] : __builtin_nan("");
+    out[2] = n;
+    out[3] = tot[7];
 }
 
-// Places for the totals in pinned host memory, which the total kernel writes itself: a copy command
-// after it took a fifth of the call (512 x 512: 36.1 -> 27.6 us).  One page for the process, 64
-// calls at a time; a call that finds no place copies.
-class HostPlaces {
-public:
-    double* take() {
-        std::lock_guard<std::mutex> lk(mu_);
-        if (!page_ && !tried_) {
-            tried_ = true;
-            if (hipHostMalloc((void**)&page_, sizeof(double) * kSums * 64, hipHostMallocPortable) != hipSuccess) {
-                page_ = nullptr;
-                (void)hipGetLastError();
-            }
-        }
-        if (!page_ || used_ == ~0ull) return nullptr;
-        const int k = __builtin_ctzll(~used_);
-        used_ |= 1ull << k;
-        return page_ + (size_t)k * kSums;
+// Pinned host memory that the GPU addresses as the host does: the total kernel writes it itself.
+bool pinned_host(const void* p) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {   // pageable
+        (void)hipGetLastError();
+        return false;
     }
-    void give(double* p) {
-        if (!p) return;
-        std::lock_guard<std::mutex> lk(mu_);
-        used_ &= ~(1ull << ((p - page_) / kSums));
-    }
-
-private:
-    std::mutex mu_;
-    double* page_ = nullptr;
-    bool tried_ = false;
-    unsigned long long used_ = 0;
-};
-
-HostPlaces& host_places() {
-    static HostPlaces* places = new HostPlaces();   // never destroyed: calls may come as the process ends
-    return *places;
+    return at.type == hipMemoryTypeHost && at.devicePointer == p && (uintptr_t)p % alignof(double) == 0;
 }
-
-struct HostPlace {
-    double* p = host_places().take();
-    ~HostPlace() { host_places().give(p); }
-};
 
 }  // namespace
 
@@ -216,25 +198,17 @@ dare_status dare_compare_to_frame(const float* image_dev, const uint8_t* frame_d
     double* partials = (double*)workspace_dev;
     hipLaunchKernelGGL(k_compare, dim3(groups), dim3(256), 0, stream, image_dev, frame_dev, w, h, tiles_x, tiles, win,
                        partials);
-    const HostPlace place;
-    hipLaunchKernelGGL(k_compare_total, dim3(1), dim3(256), 0, stream, partials, groups, place.p);
-    HIP_TRY(hipGetLastError());
-    double tot[kSums];
-    if (!place.p)
-        HIP_TRY(hipMemcpyAsync(tot, partials + (size_t)kMaxGroups * kSums, sizeof(tot), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    if (place.p) memcpy(tot, place.p, sizeof(tot));
-    const double n = tot[0];
-    double ncc = NAN;
-    if (n >= 2.0) {
-        const double saa = tot[3] - tot[1] * tot[1] / n, sbb = tot[4] - tot[2] * tot[2] / n;
-        const double sab = tot[5] - tot[1] * tot[2] / n;
-        if (saa > 0.0 && sbb > 0.0) ncc = sab / sqrt(saa * sbb);
-    }
-    out_host[0] = ncc;
-    out_host[1] = tot[7] > 0.0 ? tot[6] / tot[7] : NAN;
-    out_host[2] = n;
-    out_host[3] = tot[7];
+    // results into pinned memory need no copy command behind the kernels, a fifth of the call
+    // (512 x 512: 23 us into pinned memory, 32 into any other)
+    const bool direct = pinned_host(out_host);
+    double* const out = direct ? out_host : partials + (size_t)kMaxGroups * kSums;
+    hipLaunchKernelGGL(k_compare_total, dim3(1), dim3(256), 0, stream, partials, groups, out);
+    double res[4];
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && !direct) e = hipMemcpyAsync(res, out, sizeof(res), hipMemcpyDeviceToHost, stream);
+    const hipError_t done = hipStreamSynchronize(stream);   // whatever went before: nothing writes once this returns
+    if (e != hipSuccess || done != hipSuccess) return DARE_ERR_HIP;
+    if (!direct) memcpy(out_host, res, sizeof(res));
     return DARE_OK;
 }
 
