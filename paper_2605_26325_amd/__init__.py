@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes as ct
 import os
+import threading
 import warnings
 
 import numpy as np
@@ -440,6 +441,9 @@ class Volume:
                                                   _ptr(C.contiguous()), _stream(stream)), "dare_volume_upload_sums")
 
 
+_results = threading.local()      # compare_to_frame waits for its results, so a thread needs one place
+
+
 def compare_to_frame(image, frame, workspace=None, stream=None):
     """(NCC, mean SSIM, pixels used, windows used) of a float32 reslice against a uint8 frame of
     the same shape, both device tensors (Sec. 3's evaluation measures)."""
@@ -447,7 +451,9 @@ def compare_to_frame(image, frame, workspace=None, stream=None):
     H, W = image.shape
     if workspace is None:
         workspace = torch.empty(int(lib.dare_compare_workspace_bytes()), dtype=torch.uint8, device=image.device)
-    out = torch.empty(4, dtype=torch.float64, pin_memory=True)   # written by the kernels, no copy
+    out = getattr(_results, "out", None)      # pinned: the kernels write it, no copy
+    if out is None:
+        out = _results.out = torch.empty(4, dtype=torch.float64, pin_memory=True)
     _check(lib.dare_compare_to_frame(_ptr(image.contiguous()), _ptr(frame.contiguous()), int(W), int(H),
                                      _ptr(workspace), int(workspace.numel()), out.data_ptr(), _stream(stream)),
            "dare_compare_to_frame", allow_warn=False)

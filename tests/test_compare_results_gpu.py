@@ -49,3 +49,28 @@ def test_source_allocates_nothing():
     src = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_26325_amd", "csrc", "dare_metrics.hip")
     with open(src) as f:
         assert not re.search(r"\bhip(Host)?Malloc|\bnew \w|\bmalloc\(", f.read())
+
+
+def test_threads_have_results_of_their_own():
+    import threading
+
+    import torch
+
+    import paper_2605_26325_amd as dare
+    note("image similarity on four threads")
+    pairs = [_inputs(torch, 60 + 9 * k, 50) for k in range(4)]
+    ref = [dare.compare_to_frame(*p) for p in pairs]
+    torch.cuda.synchronize()
+    got = [[] for _ in pairs]
+
+    def work(k):
+        s = torch.cuda.Stream()
+        for _ in range(50):
+            got[k].append(dare.compare_to_frame(*pairs[k], stream=s))
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, r in enumerate(ref):
+        assert len(got[k]) == 50 and all(np.array_equal(g, r, equal_nan=True) for g in got[k])
