@@ -412,9 +412,12 @@ dare_status dare_copy_probe(const void* src_dev, void* dst_dev, uint64_t n_bytes
  * size can be allocated in the arena; each tick uploads its request table,
  * replays a captured graph of the batched reslice on a free stream (ticks on
  * different streams overlap on the device), then copies every result into its
- * `host_out` buffer (pinned host memory keeps the copy asynchronous; a device
- * buffer on the server's GPU keeps the result there, with no transfer over
- * the host link).
+ * `host_out` buffer (pinned host memory keeps the copy asynchronous).  A device
+ * buffer on the server's GPU keeps the result there, with no transfer over the
+ * host link: the tick's kernels write it themselves, so it changes while its
+ * ticket is pending and holds part of a result if the tick fails.  Where device
+ * buffers of outstanding requests overlap, results are copied instead, in
+ * request order.
  * Volumes are admitted against a second budget, `volume_budget_bytes`: the
  * device bytes of the resident volumes' arenas (Sec. 4 names dataset size
  * against GPU memory as the limit to plan for); a removed volume returns its
@@ -474,7 +477,7 @@ dare_status dare_server_volume_bytes(dare_server* s, uint64_t* resident_bytes, i
 /* Queue a request.  host_out (required) receives height*width float32,
  * row-major, NaN where unassigned, once the request completes: host memory
  * (pinned or pageable) or device memory of the server's GPU, which must stay
- * valid until the ticket completes.  Returns
+ * valid, and a device buffer unused by others, until the ticket completes.  Returns
  * QUEUE_FULL when max_queue requests wait, and INVALID_ARG when the request
  * can never fit the arena's result space or one tick. */
 dare_status dare_server_submit(dare_server* s, int32_t volume_id, const dare_slice_spec* spec,
