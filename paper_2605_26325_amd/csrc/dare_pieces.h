@@ -19,6 +19,16 @@ inline int tile_pieces(double pitch_vox) {
     return (16 / edge) * (16 / edge);
 }
 
+// Lattice points per axis that a piece of `edge` pixels squared takes at most, wherever it falls: its cells
+// span at most its extent's floor plus one, hence that plus three.  `step`: voxels per pixel along
+// the axis, |i step| + |j step|; `place`: the largest magnitude, in voxels, that enters the
+// positions, whose four roundings of 2^-53 each move the first and the last one.  (A margin of 1e-6
+// voxels alone can be exceeded from about 1e9 voxels off the world's origin.)
+constexpr int piece_points(int edge, double step, double place) {
+    const double ext = (double)(edge - 1) * step * (1.0 + 1e-9) + 1e-6 + 1e-15 * place;
+    return edge == 1 ? 2 : (int)(ext < 1024.0 ? ext : 1024.0) + 3;
+}
+
 // Workgroups per tile for `tiles` tiles of `pieces` pieces: up to 64 workgroups per CU in all.
 inline int tile_parts(int64_t tiles, int pieces) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(pieces, 16384 / std::max<int64_t>(tiles, 1)));

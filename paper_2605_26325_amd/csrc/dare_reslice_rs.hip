@@ -545,15 +545,15 @@ __device__ __forceinline__ void wide_tile(const VolDev* __restrict__ vd, const S
         if (part == 0) nan_piece<NT>(s, i0, j0, t.ni, t.nj);
         return;
     }
-    // the largest piece whose box fits wherever it falls: a piece's cells span at most its
-    // extent's floor plus one, hence that plus three lattice points; one pixel has two
+    // the largest piece whose box fits wherever it falls (a single pixel's does)
     int edge = kTile / 2;
     for (; edge > 1; edge >>= 1) {
         int len[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const double ext = (double)(edge - 1) * (fabs(q.sx * q.e0[a]) + fabs(q.sy * q.e1[a])) * q.inv_h;
-            len[a] = ui((int)fmin(ext * (1.0 + 1e-9) + 1e-6, 1024.0) + 3);
+            const double ex = fabs(q.sx * q.e0[a]), ey = fabs(q.sy * q.e1[a]);
+            const double place = fabs(q.t[a]) + fabs(q.o[a]) + (double)s.W * ex + (double)s.H * ey;
+            len[a] = ui(piece_points(edge, (ex + ey) * q.inv_h, place * q.inv_h));
         }
         if (wide_fits<R>(len, dax, kactp)) break;
     }

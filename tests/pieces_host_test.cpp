@@ -1,6 +1,7 @@
 // Host test of the split of coarse reslices over workgroups: row_tiles holds every tile with a pixel
 // in reach of the grid, and the tiles of a batch that hold work in pieces get several workgroups each,
-// however large the batch, while all others get one.
+// however large the batch, while all others get one; a piece's lattice points never exceed their bound,
+// however far from the world's origin it lies.
 #include <cstdio>
 #include <random>
 
@@ -60,6 +61,26 @@ int main() {
                     CHECK(!in || (i / 16 >= t0 && i / 16 <= t1));
                 }
         }
+    }
+    for (int trial = 0; trial < 4000000; ++trial) {   // positions as the kernel computes them, along one axis
+        std::uniform_real_distribution<double> u(0.0, 1.0);
+        const double far = std::pow(10.0, 16.0 * u(g)), h = 0.125, inv_h = 1.0 / h;
+        const double o = far * (u(g) < 0.5 ? -1.0 : 1.0) * (0.5 + 0.5 * u(g)), e0 = 1.0 - 2.0 * u(g), e1 = 1.0 - 2.0 * u(g);
+        const int edge = 1 << (g() % 4), whole = 1 + (int)(g() % 8), i0 = edge * (int)(g() % 30), j0 = edge * (int)(g() % 30);
+        // extents about whole numbers of voxels, where the roundings decide
+        const double sx = whole * h / (std::max(edge - 1, 1) * (std::fabs(e0) + std::fabs(e1)) + 1e-300);
+        const double t = o + h * (20.0 * u(g) - 10.0);
+        double lo = 0.0, hi = 0.0;
+        for (int k = 0; k < 4; ++k) {
+            const double is = (double)(i0 + (k & 1 ? edge - 1 : 0)) * sx, js = (double)(j0 + (k & 2 ? edge - 1 : 0)) * sx;
+            const double p = (t + is * e0) + js * e1, c = std::floor((p - o) * inv_h);
+            lo = k ? std::min(lo, c) : c;
+            hi = k ? std::max(hi, c) : c;
+        }
+        const double place = std::fabs(t) + std::fabs(o) + 512.0 * sx * (std::fabs(e0) + std::fabs(e1));
+        const int points = piece_points(edge, sx * (std::fabs(e0) + std::fabs(e1)) * inv_h, place * inv_h);
+        CHECK(hi - lo + 2.0 <= points || points >= 1024);
+        CHECK(far > 1e4 || points <= whole + (edge > 1 ? 4 : 3));
     }
     CHECK(tile_pieces(0.5) == 1 && tile_pieces(1.1) == 4 && tile_pieces(16.0) == 256 && tile_pieces(1e30) == 256);
     for (int n : {1, 4, 16, 64, 400}) {       // coarse slices of a batch, and as many fine ones
