@@ -118,7 +118,7 @@ struct VolView {
 // Per-slice reslice setup: composed pose, surviving bins and their Eq. 2 weights, and the
 // plane frame used by the footprint tests.
 struct SliceCore {
-    double T[12];                         // rows 0..2 of the image pose T = P . C
+    double reserved[12];                  // unused; callers' batch workspaces are sized with it
     float fm[3], fu[3], fw[3];            // unit normal and in-plane unit axes, voxel units
     float lu, lw;                         // voxels per pixel step along the two in-plane axes
     int dax;                              // dominant axis of the normal

@@ -68,15 +68,11 @@ __device__ __forceinline__ void slice_pose(const VolDev* __restrict__ vd, const 
 
 // One wave: the slice pose, and Eq. 1 / thresholds / Eq. 2 per bin (lane b takes bin b), the
 // survivors compacted into act_bin / act_w.  Returns the number of surviving bins (every lane);
-// lane 0 stores T and kact.
+// lane 0 stores kact.
 __device__ __forceinline__ int slice_gates(const VolDev* __restrict__ vd, const SliceArgs& s, SetupLds& sh,
                                            double T[12]) {
     const int lane = threadIdx.x & 63;
     slice_pose(vd, s, T);
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) sh.T[k] = T[k];
-    }
     // every lane reads its representative unconditionally: one memory round trip, not two
     const int K = vd->st.K;
     double rn[3], rx[3];
