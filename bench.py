@@ -45,7 +45,7 @@ PAIR_BYTES = {"f32": 8, "bf16": 4, "f16": 4, "fp8": 2}
 # are used only while these are unchanged
 RESLICE_SOURCES = ("dare_tiles.hip", "dare_batch.hip", "dare_batch.h", "dare_reslice_dev.h", "dare_codec.h",
                    "dare_internal.h")
-COMPOUND_SOURCES = ("dare_compound.hip", "dare_internal.h")
+COMPOUND_SOURCES = ("dare_compound.hip", "dare_patches.h", "dare_internal.h")
 
 
 def log(msg):

@@ -20,12 +20,12 @@
 // Where all 8 corners are valid the tent weights sum to 1 and the blend is the trilinear
 // interpolation (nested lerps); a NaN corner sends the pixel to the sums over its valid corners.
 //
-// A single reslice launches one workgroup per 16 x 16 tile; each workgroup evaluates the
-// request setup and its tile's record itself, since no other memory holds them: the bins on one
-// wave and the plane and tile geometry on another, at the same time.  A batch
-// runs the request setup and the tile records in a pass of its own (`k_tiles_setup`: a few
-// workgroups per request, one thread per tile; it also appends the units to a list), then one
-// persistent kernel over all staged units (`k_tiles`), which reads both records through scalar
+// A single reslice launches one workgroup per 16 x 16 tile; each workgroup evaluates the request
+// setup and its tile's record itself, since no other memory holds them, on its four waves at once
+// (the bins; the plane; the tile's box; the slab and the box's bound).  A batch runs the request
+// setup and the tile records in a pass of its own (`k_tiles_setup`: a few workgroups per request,
+// one thread per tile; it also appends the units to a list), then one persistent kernel over all
+// staged units (`k_tiles`), which reads both records through scalar
 // loads, with tiles of 32 x 32 pixels wherever their voxel box fits the LDS budget.  The
 // per-voxel and per-pixel arithmetic does not depend on the tile, so a request gives the same
 // bits alone and in a batch.  Requests whose pixels are too coarse for staging to pay (a 16 x 16
@@ -44,7 +44,7 @@ constexpr int kColsMax = 1024;       // box columns per tile
 constexpr int kSlotsMax = 1280;      // (box brick, bin) table entries per tile
 constexpr int kRunSpan = 127;        // box voxels along the dominant axis, less one, at most
 constexpr int kThreadsBatch = 256;   // threads of a batch workgroup
-constexpr int kSetupThreads = 256;   // threads of a batch setup workgroup (one request at a time)
+constexpr int kSetupThreads = 256;   // threads of a batch setup workgroup (a share of one request's tiles)
 constexpr int kTileBig = 32;         // batched tile edge where the box fits
 constexpr int kFillRun = 4096;       // pixels per unit of a batched request that is all NaN
 
@@ -631,7 +631,7 @@ __device__ __forceinline__ void stage_pixels(const SliceRec& rec, const TileRec&
         const float l1 = __builtin_fmaf(fr[PAX], lq[3] - lq[2], lq[2]);
         float val = __builtin_fmaf(fr[QAX], l1 - l0, l0);
         if (__builtin_isnan(val)) {
-            // the low voxel's weight from FP64 (tent_weight at R = 1)
+            // the low voxel's weight from FP64, so that it stays positive where it is (as in pixel_direct)
             float gr[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) gr[a] = (float)((double)b[a] + 1.0 - c[a]);
@@ -735,8 +735,8 @@ __device__ __forceinline__ void run_tile(const SliceRec& rec, const TileRec& tr,
     stage_tile_pixels<DT, NT>(rec, tr, tl);
 }
 
-// Single reslice: one workgroup per 16 x 16 tile; wave 0 evaluates the request setup, then lane
-// 0 the tile's record.
+// Single reslice: one workgroup per 16 x 16 tile, which evaluates the request setup and the tile's
+// record on its four waves.
 template <int DT>
 __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__ vd, SliceArgs s) {
     __shared__ TileLds<DT> tl;
@@ -748,8 +748,9 @@ __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__
     // frame again for the slab thresholds and the box's bound; then, again on a wave each, the
     // parts that need them together.  The workgroups of a launch are all in this phase at once, so
     // its chain is paid in full: on three waves and one lane for the second part the two took 1.8 + 1.1
-    // us, now 1.85 + 0.43; with the table reads past the box's entries left out too (they cost
-    // issue slots), 16 slices of 512 x 512 went from 153.2 to 150.6 us.
+    // us, now 1.85 + 0.43.  With the table reads past the box's entries left out too (they cost
+    // issue slots), 16 slices of 512 x 512 take 150.3 us where they took 154.0, timed in turn; one of
+    // 128 x 128 takes the 9.1 us that it took, mostly its launch.
     __shared__ int fit, bound;
     double T[12];
     if (threadIdx.x < 64) {
@@ -802,7 +803,7 @@ __global__ void __launch_bounds__(256) k_reslice_tile(const VolDev* __restrict__
 // of `tiles` (counts[0]), the other requests' units (request, tile) from the back of `units`
 // (counts[2]: entry k at cap - 1 - k), so that each kind runs in a kernel of its own.  Latency bounds
 // it: with the record on one wave and lane and one workgroup per request, 4 requests of 512 x 512
-// took 15.0 us, now 7.8 us (64 requests 9.3 and 8.5).
+// took 15.0 us, now 7.8 us (64 requests 9.3 and 8.5 us, of the 143 us of such a call).
 __global__ void __launch_bounds__(kSetupThreads) k_tiles_setup(const BatchReq* __restrict__ reqs,
                                                                SliceRec* __restrict__ recs, int2* __restrict__ units,
                                                                TileRec* __restrict__ tiles, int* __restrict__ counts,
