@@ -462,8 +462,8 @@ __device__ __forceinline__ void merge_pixels(int& place, int local, uint32_t& ad
 }
 
 // K4: add each pixel's intensity and a count to its (bin, voxel).  Bound by the rate at which
-// memory takes the atomic requests (they go past the L2s, which do not share lines between XCDs):
-// 40 M requests of up to 64 bytes for the 100 M in-grid pixels of 1800 frames of 256^2, 1660 us.  With
+// memory takes the atomic requests (all go past the L2s, which do not share lines between XCDs):
+// 37 M requests of up to 64 bytes for the 100 M in-grid pixels of 1800 frames of 256^2, 1660 us.  With
 // the wave's 64 pixels along a row instead of an 8 x 8 block it was 2730 us.  Merging pixels of one
 // voxel first takes 300 fan frames (about 6 pixels a voxel) from 523 to 188 us.
 template <bool FAN>
