@@ -193,6 +193,8 @@ int volume_radius(const dare_volume* v) { return (int)v->p.radius_vox; }
 int volume_device_id(const dare_volume* v) { return v->device; }
 uint64_t volume_arena_size(const dare_volume* v) { return v->arena_bytes; }
 void add_staged_units(const dare_volume* v, const dare_slice_spec* s, int r, StagedUnits<int2>& u) {
+    const int pieces = tile_pieces(pitch_vox(v, s));
+    if (pieces == 1) return u.add_fine(r, s->width, s->height);
     double T[16];
     compose_host(s->probe_pose, v->g.calib, T);
     PlaneView w;
@@ -205,7 +207,7 @@ void add_staged_units(const dare_volume* v, const dare_slice_spec* s, int r, Sta
     w.W = s->width;
     w.H = s->height;
     w.reach = v->p.radius_vox;
-    u.add(w, r, pitch_vox(v, s));
+    u.add_coarse(w, r, pieces);
 }
 dare_status check_slice_spec(const dare_slice_spec* s) { return check_spec(s); }
 bool rigid_pose(const double* M) { return rigid(M); }

@@ -72,25 +72,35 @@ template <class Unit>
 struct StagedUnits {
     std::vector<Unit> coarse, fine;
     int most_pieces = 1;
-    // The tiles of request `r`.
-    void add(const PlaneView& v, int r, double pitch_vox) {
-        const int pieces = tile_pieces(pitch_vox), tx = (v.W + 15) / 16, ty = (v.H + 15) / 16;
+    // The tiles of request `r`, staged in one piece each.
+    void add_fine(int r, int W, int H) {
+        const int n = ((W + 15) / 16) * ((H + 15) / 16);
+        for (int t = 0; t < n; ++t) fine.push_back(Unit{r, t});
+    }
+    // The tiles of request `r`, in `pieces` pieces each where they hold work.
+    void add_coarse(const PlaneView& v, int r, int pieces) {
+        const int tx = (v.W + 15) / 16, ty = (v.H + 15) / 16;
         most_pieces = std::max(most_pieces, pieces);
         for (int y = 0; y < ty; ++y) {
-            int t0 = 0, t1 = -1;
-            if (pieces > 1) row_tiles(v, y, t0, t1);
+            int t0, t1;
+            row_tiles(v, y, t0, t1);
             for (int x = 0; x < tx; ++x) (x >= t0 && x <= t1 ? coarse : fine).push_back(Unit{r, y * tx + x});
         }
     }
     // The unit list in the kernel's order and its counts (dare_batch.h; counts[1] is the caller's);
     // returns the workgroups that it can use.
-    int finish(int32_t counts[4], std::vector<Unit>& units) const {
-        units = coarse;
-        units.insert(units.end(), fine.begin(), fine.end());
-        counts[0] = (int32_t)units.size();
+    int finish(int32_t counts[4], std::vector<Unit>& units) {
+        counts[0] = (int32_t)(coarse.size() + fine.size());
         counts[2] = (int32_t)coarse.size();
         counts[3] = tile_parts((int64_t)coarse.size(), most_pieces);
-        return (int)std::min<int64_t>((int64_t)fine.size() + (int64_t)coarse.size() * counts[3], 65535);
+        const int64_t groups = (int64_t)fine.size() + (int64_t)coarse.size() * counts[3];
+        if (coarse.empty()) {
+            units.swap(fine);
+        } else {
+            units.swap(coarse);
+            units.insert(units.end(), fine.begin(), fine.end());
+        }
+        return (int)std::min<int64_t>(groups, 65535);
     }
 };
 

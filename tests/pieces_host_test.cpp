@@ -90,7 +90,8 @@ int main() {
         int64_t tiles = 0;
         for (int r = 0; r < 2 * n; ++r) {
             const PlaneView v = random_view(g, 512, 300, 256, r % 2 ? 0.5 : 16.0);
-            u.add(v, r, r % 2 ? 0.5 : 16.0);
+            if (r % 2) u.add_fine(r, v.W, v.H);
+            else u.add_coarse(v, r, tile_pieces(16.0));
             tiles += 32 * 19;
         }
         const int grid = u.finish(counts, units);
