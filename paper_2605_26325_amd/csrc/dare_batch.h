@@ -16,9 +16,9 @@ struct BatchReq {
 
 // Batch header at the start of a workspace: int32 counts, then the radius-1 tile kernel's claim
 // counter of each of the 8 XCDs, each on a 256-byte line of its own (claims[x][0]: counters that
-// share a line serialise each other's atomics).  Radius 1: counts {units, requests, units at the
-// list's back, 0}; the units are appended on the device, so counts[0] and counts[2] must be
-// uploaded as 0, and so must the claims.  Other radii: {units, requests, units at the list's front
+// share a line serialise each other's atomics).  Radius 1: counts {staged units, requests, units at
+// the list's back, units at its front}; all but the requests are appended on the device, so they
+// must be uploaded as 0, and so must the claims.  Other radii: {units, requests, units at the list's front
 // that take several workgroups, how many}, uploaded with the unit list.  The kernels address the header as int32 words from counts.
 constexpr int kClaimStride = 64;          // int32 words between two XCDs' claim counters
 struct BatchHeader {
@@ -64,7 +64,7 @@ struct TileRec {
 hipError_t launch_reslice_tile(const VolDev* vd, int dtype, const SliceArgs& s, hipStream_t stream);
 // Radius 1, a batch: setup pass (a few workgroups per request: the request record, then one tile
 // record per thread) + persistent tile kernel + the per-pixel kernel for requests too coarse to stage.
-// `counts[0]`, `counts[2]` and the claims must hold 0 and `counts[1]` the number of requests when the stream
+// `counts[0]`, `counts[2]`, `counts[3]` and the claims must hold 0 and `counts[1]` the number of requests when the stream
 // reaches the launch; `units` and `tiles` hold `cap` entries, at least tile_units_max() per
 // request in all.
 hipError_t launch_tiles_batch(int dtype, const BatchReq* reqs, SliceRec* recs, int2* units, TileRec* tiles,
