@@ -318,6 +318,9 @@ __device__ __forceinline__ void mark_one(VolDev* vd, int64_t e) {
 // workgroup 480), then the chain of a mark's read, exchange and store, gone through once per 1024
 // pixels (2730 us when the four blocks marked in turn).  One mark per run of a 64-pixel row, each
 // with its own addition, took 1190 us; 30 frames of 512^2 into resident bricks 254 -> 71 us.
+// An entry that finds no place in 24 steps is marked at once, which a whole wave waits for: with 8
+// steps a set two thirds full (20 x 20 pixels 5 voxels apart) turned enough of them away for a call
+// of 1200 frames to take 136 us, not 113; 24 are no slower where the set is full (a pixel a brick).
 constexpr int kMarkSet = 256;
 template <bool FAN>
 __device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, const PatchShape& shape, double sx, double sy, const FanArgs* fan, int f0) {
@@ -341,7 +344,7 @@ __device__ __forceinline__ void mark_patch(VolDev* vd, int w, int h, const Patch
         bool mine = e >= 0 && !(lane >= 1 && left == e) && !(lane >= 8 && up == e);
         if (mine) {
             uint32_t at = ((uint32_t)e * 2654435761u) >> 24;
-            for (int probe = 0; probe < 8; ++probe, at = (at + 1) & (kMarkSet - 1)) {
+            for (int probe = 0; probe < 24; ++probe, at = (at + 1) & (kMarkSet - 1)) {
                 const int was = atomicCAS(&set[at], -1, e);
                 mine = was != -1 && was != e;
                 if (!mine) break;
