@@ -826,7 +826,8 @@ __global__ void __launch_bounds__(kSetupThreads) k_tiles_setup(const BatchReq* _
     __shared__ SliceRec rec;
     __shared__ int fit[2], bound[2];      // tile edges kTileBig, 16
     __shared__ int sh[3];                 // this workgroup's first and last unit, first entry of its units
-    __shared__ int cls[2][kSetupThreads / 64], at[2];   // per-pixel units: {near the grid, away from it}
+    __shared__ int cls[kSetupThreads / 64];   // per-pixel units near the grid, by wave
+    __shared__ int at[2];                 // places of those {near the grid, away from it}
     const int n = counts[1] * split;
     for (int b = blockIdx.x; b < n; b += gridDim.x) {
         const int r = b / split, part = b - r * split;
@@ -890,27 +891,42 @@ __global__ void __launch_bounds__(kSetupThreads) k_tiles_setup(const BatchReq* _
         } else if (mode == 0) {
             for (int t = k; t < k1; t += kSetupThreads) units[base + t - k0] = make_int2(r, ~t);
         } else {
-            const int wave = (int)threadIdx.x >> 6;
-            for (int t0 = k0; t0 < k1; t0 += kSetupThreads) {
-                const int t = t0 + (int)threadIdx.x;
-                const bool near = t < k1 && near_grid(pl, t);
-                const unsigned long long m0 = __ballot(near), m1 = __ballot(t < k1 && !near);
-                if ((threadIdx.x & 63) == 0) {
-                    cls[0][wave] = __popcll(m0);
-                    cls[1][wave] = __popcll(m1);
+            // places for 32 tiles a thread at once: one addition to each counter (one slice of 2000 x 2000
+            // 6 voxels apart: 39 us, 41 with an addition for each tile a thread, 35 if listed unsorted)
+            const int lane = threadIdx.x & 63;
+            for (int g0 = k0; g0 < k1; g0 += 32 * kSetupThreads) {
+                const int g1 = min(k1, g0 + 32 * kSetupThreads);
+                uint32_t bits = 0;        // bit c: tile g0 + c * kSetupThreads + thread is near
+                int mine = 0;
+                for (int t0 = g0, c = 0; t0 < g1; t0 += kSetupThreads, ++c) {
+                    const int t = t0 + (int)threadIdx.x;
+                    const bool near = t < g1 && near_grid(pl, t);
+                    bits |= (near ? 1u : 0u) << c;
+                    mine += __popcll(__ballot(near));
                 }
+                if (lane == 0) cls[threadIdx.x >> 6] = mine;
                 __syncthreads();
                 if (threadIdx.x < 2) {
                     int sum = 0;
-                    for (int w = 0; w < kSetupThreads / 64; ++w) sum += cls[threadIdx.x][w];
+                    for (int w = 0; w < kSetupThreads / 64; ++w) sum += cls[w];
+                    if (threadIdx.x == 1) sum = g1 - g0 - sum;
                     at[threadIdx.x] = sum ? atomicAdd(counts + 2 + threadIdx.x, sum) : 0;
                 }
                 __syncthreads();
-                const int c = near ? 0 : 1;
-                int e = at[c] + __popcll((near ? m0 : m1) & ((1ull << (threadIdx.x & 63)) - 1ull));
-                for (int w = 0; w < wave; ++w) e += cls[c][w];
-                if (t < k1) units[near ? cap - 1 - e : e] = make_int2(r, t);
-                __syncthreads();
+                for (int t0 = g0, c = 0; t0 < g1; t0 += kSetupThreads, ++c) {
+                    const int t = t0 + (int)threadIdx.x;
+                    const bool near = bits >> c & 1u;
+                    const unsigned long long m0 = __ballot(near), m1 = __ballot(t < g1 && !near);
+                    int e0 = 0, e1 = 0;
+                    if (lane == 0) {
+                        if (m0) e0 = atomicAdd(&at[0], __popcll(m0));
+                        if (m1) e1 = atomicAdd(&at[1], __popcll(m1));
+                    }
+                    const unsigned long long below = (1ull << lane) - 1ull;
+                    e0 = __builtin_amdgcn_readfirstlane(e0) + __popcll(m0 & below);
+                    e1 = __builtin_amdgcn_readfirstlane(e1) + __popcll(m1 & below);
+                    if (t < g1) units[near ? cap - 1 - e0 : e1] = make_int2(r, t);
+                }
             }
         }
         __syncthreads();

@@ -42,7 +42,8 @@ def test_coarse_mixes(dtype):
     calls = [[spec(333, 300, 2.6), spec(64, 50, 0.5), spec(90, 70, 1.0, angle=gated), spec(17, 400, 9.0), spec(301, 299, 30.0),
               spec(200, 200, 6.0), spec(40, 40, 6.0, shift=500.0), spec(1, 1, 4.0), spec(600, 500, 4.0)],
              [spec(33, 31, 3.0), spec(400, 90, 2.2, angle=gated)],
-             [spec(260, 270, 3.3) for _ in range(7)] + [spec(70, 300, 0.6)]]
+             [spec(260, 270, 3.3) for _ in range(7)] + [spec(70, 300, 0.6)],
+             [spec(2000, 1500, 2.4)], [spec(4200, 4100, 3.0)]]   # 1469 and 8449 tiles for each workgroup
     ws = torch.empty(max(dare.dare_reslice_batch_workspace_bytes([vol] * len(c), c) for c in calls), dtype=torch.uint8,
                      device="cuda")
     seen = 0
